@@ -123,11 +123,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, int64_
 // it (it then goes into the instruction's scalar offset).  A stageable view also names the kNV complex64 vectors it
 // reads (rsrc(j)) and forms the element from their values (combine); own(i, v) reads them
 // at element i.
+// Cache policy kL2 (the sc1 bit, agent scope): the read misses this CU's L1 and is served by
+// the L2.  Vectors that other workgroups of the launch write are read this way, so a wait
+// needs no invalidate after it: the agent-scope invalidate walks the whole L2 and took 13.5 of
+// the 14.9 us of a barrier of 8 workgroups (1.0 us without it).
+constexpr int kL2 = 16;
+template <int POLICY = 0>
 __device__ __forceinline__ float2 buf_ld2(__amdgpu_buffer_rsrc_t r, uint32_t i) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, i * 8u, 0, 0));
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, i * 8u, 0, POLICY));
 }
+template <int POLICY = 0>
 __device__ __forceinline__ float2 buf_ld2b(__amdgpu_buffer_rsrc_t r, uint32_t vb, uint32_t sb) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vb, sb, 0));
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vb, sb, POLICY));
 }
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -144,28 +151,33 @@ __device__ __forceinline__ u32x4 pack2(float2 a, float2 b) {
   const u32x2 x = __builtin_bit_cast(u32x2, a), y = __builtin_bit_cast(u32x2, b);
   return u32x4{x.x, x.y, y.x, y.y};
 }
-struct SrcBuf {   // complex64 vector
+template <int POL>
+struct SrcBufT {   // complex64 vector
   __amdgpu_buffer_rsrc_t r;
+  static constexpr int kPol = POL;
   static constexpr int kNV = 1;
   static constexpr bool kStageable = true;
   static constexpr bool kPairs = true;
   using Raw = float2;
   using Raw2 = u32x4;
-  __device__ __forceinline__ Raw load(uint32_t i) const { return buf_ld2(r, i); }
-  __device__ __forceinline__ Raw load_b(uint32_t vb, uint32_t sb) const { return buf_ld2b(r, vb, sb); }
+  __device__ __forceinline__ Raw load(uint32_t i) const { return buf_ld2<POL>(r, i); }
+  __device__ __forceinline__ Raw load_b(uint32_t vb, uint32_t sb) const { return buf_ld2b<POL>(r, vb, sb); }
   __device__ __forceinline__ float2 value(Raw v) const { return v; }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int) const { return r; }
   __device__ __forceinline__ float2 combine(const float2* v) const { return v[0]; }
-  __device__ __forceinline__ void own(uint32_t i, float2* v) const { v[0] = buf_ld2(r, i); }
+  __device__ __forceinline__ void own(uint32_t i, float2* v) const { v[0] = buf_ld2<POL>(r, i); }
   // pairs: the elements at byte offsets vb + sb and vb + sb + 8
-  __device__ __forceinline__ Raw2 load2_b(uint32_t vb, uint32_t sb) const { return buf_ld4b(r, vb, sb); }
+  __device__ __forceinline__ Raw2 load2_b(uint32_t vb, uint32_t sb) const { return buf_ld4b<POL>(r, vb, sb); }
   __device__ __forceinline__ void value2(const Raw2& v, float2& a, float2& b) const { unpack2(v, a, b); }
   __device__ __forceinline__ void own2(uint32_t i, float2* a, float2* b) const {
-    unpack2(buf_ld4b(r, i * 8u, 0), a[0], b[0]);
+    unpack2(buf_ld4b<POL>(r, i * 8u, 0), a[0], b[0]);
   }
 };
+using SrcBuf = SrcBufT<0>;       // written before the launch
+using SrcShared = SrcBufT<kL2>;  // written by the frame's workgroups during the launch
 struct SrcBf16 {  // complex stored as a bf16 pair per element (not staged)
   __amdgpu_buffer_rsrc_t r;
+  static constexpr int kPol = 0;
   static constexpr int kNV = 1;
   static constexpr bool kStageable = false;
   static constexpr bool kPairs = false;
@@ -184,28 +196,29 @@ struct SrcBf16 {  // complex stored as a bf16 pair per element (not staged)
 struct SrcDir {   // the new direction c + beta p, formed from c and the old p
   __amdgpu_buffer_rsrc_t c, p;
   float beta;
+  static constexpr int kPol = kL2;
   static constexpr int kNV = 2;
   static constexpr bool kStageable = true;
   struct Raw {
     float2 c, p;
   };
-  __device__ __forceinline__ Raw load(uint32_t i) const { return Raw{buf_ld2(c, i), buf_ld2(p, i)}; }
+  __device__ __forceinline__ Raw load(uint32_t i) const { return Raw{buf_ld2<kL2>(c, i), buf_ld2<kL2>(p, i)}; }
   __device__ __forceinline__ Raw load_b(uint32_t vb, uint32_t sb) const {
-    return Raw{buf_ld2b(c, vb, sb), buf_ld2b(p, vb, sb)};
+    return Raw{buf_ld2b<kL2>(c, vb, sb), buf_ld2b<kL2>(p, vb, sb)};
   }
   __device__ __forceinline__ float2 value(const Raw& v) const { return axpyf(beta, v.p, v.c); }
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int j) const { return j == 0 ? c : p; }
   __device__ __forceinline__ float2 combine(const float2* v) const { return axpyf(beta, v[1], v[0]); }
   __device__ __forceinline__ void own(uint32_t i, float2* v) const {
-    v[0] = buf_ld2(c, i);
-    v[1] = buf_ld2(p, i);
+    v[0] = buf_ld2<kL2>(c, i);
+    v[1] = buf_ld2<kL2>(p, i);
   }
   static constexpr bool kPairs = true;
   struct Raw2 {
     u32x4 c, p;
   };
   __device__ __forceinline__ Raw2 load2_b(uint32_t vb, uint32_t sb) const {
-    return Raw2{buf_ld4b(c, vb, sb), buf_ld4b(p, vb, sb)};
+    return Raw2{buf_ld4b<kL2>(c, vb, sb), buf_ld4b<kL2>(p, vb, sb)};
   }
   __device__ __forceinline__ void value2(const Raw2& v, float2& a, float2& b) const {
     float2 c0, c1, p0, p1;
@@ -215,8 +228,8 @@ struct SrcDir {   // the new direction c + beta p, formed from c and the old p
     b = axpyf(beta, p1, c1);
   }
   __device__ __forceinline__ void own2(uint32_t i, float2* a, float2* b) const {
-    unpack2(buf_ld4b(c, i * 8u, 0), a[0], b[0]);
-    unpack2(buf_ld4b(p, i * 8u, 0), a[1], b[1]);
+    unpack2(buf_ld4b<kL2>(c, i * 8u, 0), a[0], b[0]);
+    unpack2(buf_ld4b<kL2>(p, i * 8u, 0), a[1], b[1]);
   }
 };
 struct SrcLds {   // complex64 vector in LDS
@@ -483,20 +496,26 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
   __syncthreads();
   return s;
 }
+// a value that another workgroup of this launch stored: read past this CU's L1
+template <class T>
+__device__ __forceinline__ T shared_ld(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // sum of the T per-tile partials of a frame, in FP32 and in tile order, by every thread:
 // every workgroup of the frame forms the same value, independent of the rest of the batch
 __device__ __forceinline__ float tile_sum(const float* part, int T) {
-  // loads in groups of 8 in flight together; the sum runs in tile order
+  // loads in groups of 8 in flight together; the sum runs in tile order.  Agent-scope loads:
+  // the partials are other workgroups' stores, which this CU's L1 may hold stale
   float s = 0.f;
   int i = 0;
   for (; i + 8 <= T; i += 8) {
     float v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = part[i + j];
+    for (int j = 0; j < 8; ++j) v[j] = shared_ld(part + i + j);
 #pragma unroll
     for (int j = 0; j < 8; ++j) s = __fadd_rn(s, v[j]);
   }
-  for (; i < T; ++i) s = __fadd_rn(s, part[i]);
+  for (; i < T; ++i) s = __fadd_rn(s, shared_ld(part + i));
   return s;
 }
 __device__ __forceinline__ double tile_sum_d(const double* part, int T) {
@@ -505,11 +524,11 @@ __device__ __forceinline__ double tile_sum_d(const double* part, int T) {
   for (; i + 8 <= T; i += 8) {
     double v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = part[i + j];
+    for (int j = 0; j < 8; ++j) v[j] = shared_ld(part + i + j);
 #pragma unroll
     for (int j = 0; j < 8; ++j) s += v[j];
   }
-  for (; i < T; ++i) s += part[i];
+  for (; i < T; ++i) s += shared_ld(part + i);
   return s;
 }
 
@@ -520,20 +539,16 @@ __device__ __forceinline__ double tile_sum_d(const double* part, int T) {
 //  XCD-local (all workgroups of the frame run on one XCD, whose L2 they share): every
 //  thread waits for its own stores to reach the L2 (s_waitcnt vmcnt(0); no L2 write-back,
 //  so the data stays in the shared L2), one lane counts the arrival with an L2 atomic and
-//  polls the count with L2 atomics, and after the workgroup meets again every thread
-//  takes an agent-scope acquire (buffer_inv sc1), which drops this CU's L1.  The
-//  workgroup-scope invalidate (buffer_inv sc0) is not enough: outside threadgroup-split
-//  mode it leaves L1 lines written by other CUs stale (measured).
+//  polls the count with L2 atomics.  Nothing is invalidated afterwards: what other
+//  workgroups store is read past this CU's L1 (SrcShared, shared_ld; see kL2), and the
+//  workgroup's own stores are coherent in its CU's L1.
 //  Agent (fallback, any placement): agent-scope release and acquire fences (L2 write-back
 //  and invalidate, the L2s of different XCDs not being coherent) around an agent-scope
 //  counter.
 // The wait is bounded: after `timeout` ticks of the 100 MHz wall clock, or when another
 // workgroup has raised the launch-wide abort flag, it gives up and reports failure.
 __device__ __forceinline__ void xcd_release() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void xcd_acquire() {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
+__device__ __forceinline__ void xcd_acquire() { asm volatile("" ::: "memory"); }
 
 // Current value of a counter kept in the L2 by workgroup-scope atomics.  A plain or
 // idempotent read could be served by this CU's L1 (the compiler turns an idempotent RMW
@@ -1110,8 +1125,8 @@ __device__ __forceinline__ C cplx(decltype(C{}.x) x, decltype(C{}.x) y) {
 
 // A: the arithmetic (ArithF32 for the CG passes; ArithF64 for the true-residual refresh,
 // whose sums and coefficients are FP64 while the window holds the FP32 source).
-template <bool ADJ, class A, class Pref, class Sink>
-__device__ __forceinline__ void lds_apply_pairs(const FrameDev& F, int lb, int le, const SrcBuf& src,
+template <bool ADJ, class A, class Src, class Pref, class Sink>
+__device__ __forceinline__ void lds_apply_pairs(const FrameDev& F, int lb, int le, const Src& src,
                                                 float2* lds_gen, Pref pref, Sink sink, A = A{}) {
   using C = typename A::C;
   constexpr bool F32 = std::is_same<A, ArithF32>::value;
@@ -1156,7 +1171,7 @@ __device__ __forceinline__ void lds_apply_pairs(const FrameDev& F, int lb, int l
         sc += sc < 0 ? M : 0;
         sc -= sc >= M ? M : 0;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(src.r, (lptr<void>)(win + (c << 7)), 16,
-                                                 (uint32_t)(sr * M + sc) * 8u, 0, 0, 0);
+                                                 (uint32_t)(sr * M + sc) * 8u, 0, 0, Src::kPol);
       }
       e += kWaves << 7;
       r += dr;
@@ -1425,7 +1440,8 @@ __device__ __forceinline__ void staged_apply(const FrameDev& F, int lb, int le, 
 #pragma unroll
             for (int j = 0; j < NV; ++j)
               __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                  src.rsrc(j), (lptr<void>)(win[j].p + r * WS + ch * 32), 4, voff, 0, 0, 0);
+                  src.rsrc(j), (lptr<void>)(win[j].p + r * WS + ch * 32), 4, voff, 0, 0,
+                  Src::kPol);
           }
         }
       }
@@ -1501,7 +1517,7 @@ __device__ __forceinline__ void apply_band(const FrameDev& F, int lb, int le, fl
     return;
   }
   if constexpr (GM == kGmLds && SD == kDNone) {
-    if constexpr (std::is_same<Src, SrcBuf>::value) {
+    if constexpr (std::is_same<Src, SrcBuf>::value || std::is_same<Src, SrcShared>::value) {
       if (pairs_ok(F) && lds_window_fits(F, lb, le)) {   // same bits as the direct pairs
         static_assert(!Out::kOwn, "the windowed pairs pass no own elements");
         lds_apply_pairs<ADJ, ArithF32>(
@@ -1871,7 +1887,7 @@ __device__ __forceinline__ void refresh_u_window(const FrameDev& F, const WorkIt
                                                  const FrameVecs& V, float2* lds) {
   const int64_t E = (int64_t)F.M * F.N;
   const CVec u = cvec(F.u, E);
-  const SrcBuf xs{buf_rsrc(V.x, E * 8)};
+  const SrcShared xs{buf_rsrc(V.x, E * 8)};
   struct Y2 {
     float2 a, b;
   };
@@ -1889,7 +1905,7 @@ __device__ __forceinline__ double refresh_c_window(const FrameDev& F, const Work
   const int64_t E = (int64_t)F.M * F.N;
   const double lam = (double)F.lam;
   const CVec cv = cvec(F.c, E), xv = cvec(V.x, E);
-  const SrcBuf us{buf_rsrc(F.u, E * 8)};
+  const SrcShared us{buf_rsrc(F.u, E * 8)};
   double acc = 0.0;
   auto cval = [&](double2 v, float2 x) {
     return make_float2((float)(v.x - lam * (double)x.x), (float)(v.y - lam * (double)x.y));
@@ -2113,16 +2129,16 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
       if (!halo(rd_h)) return fail_timeout();
       // A2: t = H p' (one load per gather, or through LDS windows)
       if (kNtT && F.stream_t)
-        apply_band<false, SD, GM, RR>(F, lb, le, lds, SrcBuf{pnv.r}, OutStore<true>{tv});
+        apply_band<false, SD, GM, RR>(F, lb, le, lds, SrcShared{pnv.r}, OutStore<true>{tv});
       else
-        apply_band<false, SD, GM, RR>(F, lb, le, lds, SrcBuf{pnv.r}, OutStore<false>{tv});
+        apply_band<false, SD, GM, RR>(F, lb, le, lds, SrcShared{pnv.r}, OutStore<false>{tv});
     }
     if (!halo(rd_hh)) return fail_timeout();
 
     // ---- B: a = H^H t + lam p, partial Re(p^H a) ----
     {
       float acc = 0.f;
-      apply_band<true, SD, GM, RR>(F, lb, le, lds, SrcBuf{tv.r}, OutB{av, pnv, lam, &acc});
+      apply_band<true, SD, GM, RR>(F, lb, le, lds, SrcShared{tv.r}, OutB{av, pnv, lam, &acc});
       const float bs = block_sum(acc, red);
       if (threadIdx.x == 0) F.part_pa[wi.tile] = bs;
     }
@@ -2373,7 +2389,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     {
       float acc = 0.f;
       win_apply_any<true>(
-          F, k0, lds, SrcBuf{tv.r}, [&](uint32_t q) { return pnv.ld(q); },
+          F, k0, lds, SrcShared{tv.r}, [&](uint32_t q) { return pnv.ld(q); },
           [&](int q, float2 v, const float2& p) {
             const float2 a = axpyf(lam, p, v);
             av.st<kNtB>((uint32_t)q, a);
