@@ -189,7 +189,11 @@ typedef struct {
 otfs_status otfs_plan_info(const otfs_plan_t* plan, otfs_plan_info_t* info);
 
 /* Change the tiling (target elements per workgroup tile, >= 1, or 0 for the built-in
- * rule) and the workgroup cap of the fused kernel (0 = occupancy limit).  Takes effect at
+ * rule) and the workgroup cap of the fused kernel (0 = occupancy limit).  The built-in rule
+ * keeps the CG vectors of most frames in the registers of up to 32 workgroups; a tiling, a
+ * workgroup cap, staging, a window, or one of the flags that name a form (OTFS_LDS_GATHER,
+ * OTFS_SPLIT_DIRECTION, OTFS_NO_LDS_RESIDENT, OTFS_AGENT_BARRIER, a stored D) selects the
+ * streaming kinds, and so does a path table made on the device from a pilot.  Takes effect at
  * the next otfs_plan_bind.  Used by the autotuner. */
 otfs_status otfs_plan_set_tiling(otfs_plan_t* plan, int32_t tile_elems, int32_t max_grid);
 

@@ -10,7 +10,7 @@ on the frame shapes, the path count, the batch size and the modes (refresh, stor
 tune() searches these knobs for one batch on the current device: every candidate plan
 solves the same received frames; its fused solve is timed with HIP events on the launch
 stream (median of `reps` after a warm-up) and its estimate is checked against the default
-plan's (NMSE <= 1e-6: a candidate changes the rounding order of the per-tile partial
+plan's (the first candidate: the library's built-in launch shape) (NMSE <= 1e-6: a candidate changes the rounding order of the per-tile partial
 sums, nothing else).  The winner and the whole search table are stored in tuned.json
 beside this module, keyed by the batch signature (frame shapes, batch-size bucket, path
 bucket, modes).  Plan applies a stored winner by default (lookup()), and the serving
@@ -94,7 +94,8 @@ def candidates(frames: Sequence, cus: int = 256) -> List[Dict]:
         tiles.add(max(512, int(Etot / (cus * w))))
     tiles = sorted(t for t in tiles if t >= 512)
     pairs = any(int(f.M) % 128 == 0 for f in frames)
-    out = []
+    # the built-in choice (register-resident tiles where they apply)
+    out = [{"tile_elems": 0, "split_direction": False, "stage_bytes": 0, "lds_gather": False}]
     for te in tiles:
         out.append({"tile_elems": te, "split_direction": False, "stage_bytes": 0,
                     "lds_gather": False})

@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libotfs.so")
-SOURCES = ["kernels.hip", "dzt.hip", "plan.cpp", "server.cpp"]
+SOURCES = ["kernels.hip", "cg_tile.hip", "dzt.hip", "plan.cpp", "server.cpp"]
 ARCH = os.environ.get("OTFS_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [
@@ -21,7 +21,7 @@ HIPCC_FLAGS = [
 ]
 
 
-HEADERS = ["otfs_internal.h", "plan_internal.h"]
+HEADERS = ["otfs_internal.h", "plan_internal.h", "device_util.h"]
 
 
 def source_sha(csrc: str = None, include: str = None) -> str:

@@ -108,6 +108,14 @@ struct FrameDev {
   // all Doppler rows, and each gather pass streams the source rows through an LDS window
   // win_rc output rows at a time
   int32_t win_w, win_rc;
+  // register-resident tiles (tk_T = 0: off; the path tables are then the host's): tk_nbr row bands x tk_nbc strips of tk_tc columns
+  // (the last strip may be narrower), tk_cw columns per lane; slots: the meeting words of
+  // the tiles (4 kinds x tk_T)
+  int32_t tk_T, tk_nbr, tk_nbc, tk_tc, tk_cw, tk_elems;
+  unsigned long long* slots;
+  // the cut of the standalone applications (ap_T = 0: by the streaming items)
+  int32_t ap_T, ap_nbr, ap_nbc, ap_tc, ap_cw;
+  float2* stab;           // P x M: the H^H coefficients by output column (k_tile_tables)
   // path capacity: the P given at otfs_plan; a path table estimated on the device from a
   // pilot frame (otfs_plan_paths_from_pilot) may set P to anything in [0, pcap]
   int32_t pcap;
@@ -154,9 +162,11 @@ constexpr int kResidentBytes = 40 * 1024;       // LDS of a frame solved residen
 constexpr int kStageVecs = 2;    // vectors staged at once (phase A stages c and the old p)
 
 // One workgroup per item.  in/out are batch-wide complex64 buffers (frame at base + off).
-// lds_bytes: dynamic LDS for staged windows (0 if no frame is staged).
+// lds_bytes: dynamic LDS for staged windows (0 if no frame is staged).  skip_cut: leave the
+// frames with an apply cut out.
 hipError_t launch_apply(bool adjoint, int sd, const FrameDev* frames, const WorkItem* items,
-                        int nitems, const float2* in, float2* out, int lds_bytes, hipStream_t s);
+                        int nitems, const float2* in, float2* out, int lds_bytes, bool skip_cut,
+                        hipStream_t s);
 
 // Reset barrier counters and CG state of frames [0, nframes), the abort word and the
 // queue cursors of ngroups groups.
@@ -180,8 +190,25 @@ hipError_t launch_step_reset(const FrameDev* frames, int nframes, unsigned* abor
 // direct-fd: direct frames whose H pass forms the direction inside its gathers (batches
 // whose direct frames all have P <= kFusedDirMaxPaths)
 // windowed: frames tiled into strips whose gathers stream source rows through an LDS ring
+// tile: frames whose CG vectors live in the registers of their workgroups (cg_tile.hip)
 constexpr int kKindDirect = 0, kKindStaged = 1, kKindResident = 2, kKindDirectFD = 3,
-              kKindWindowed = 4, kKindLds = 5, kKinds = 6;
+              kKindWindowed = 4, kKindLds = 5, kKindTile = 6,
+              kKindTileSmall = 7, kKinds = 8;
+// register-resident tiles: elements of a tile per thread (kKindTileSmall: when every tile of
+// the launch is that small), tiles of a frame at most (one wave polls their meeting words,
+// one lane each), and the queue entry's frame stride
+constexpr int kTileElems = 16, kTileElemsSmall = 8, kTileMaxTiles = 32, kTileStride = 64;
+constexpr int kTileMeets = 4;   // meeting words per tile
+// H (H^H) of the frames with an apply cut: one workgroup per item {frame, tile}, windows of at
+// most lds_bytes.  nxcd: as for launch_refresh.
+hipError_t launch_apply_tile(bool adjoint, const FrameDev* frames, const int2* items, int nitems,
+                             int nxcd, const float2* in, float2* out, int lds_bytes, hipStream_t s);
+// Build stab of the frames with a cut from rtab and wtab.
+hipError_t launch_tile_tables(const FrameDev* frames, int nframes, hipStream_t s);
+const void* tile_fn(int kind);
+void launch_tile(int kind, const FrameDev* frames, const int32_t* qitems, const int2* qrange,
+                 unsigned* qhead, int ngroups, int grid, int budget, const Bases& bases,
+                 unsigned* abort_flag, uint64_t timeout, int lds_bytes, hipStream_t s);
 #ifndef OTFS_FUSED_DIR_MAX_PATHS
 #define OTFS_FUSED_DIR_MAX_PATHS 8
 #endif

@@ -172,6 +172,12 @@ void frame_scalars(const HostFrame& fr, const otfs_cg_opts& o, int tiles, const 
   d->stream_t = (int64_t)fr.M * fr.N >= kStreamTElems ? 1 : 0;
   d->win_w = geo.win_w;
   d->win_rc = geo.win_rc;
+  d->tk_T = geo.tk_T;
+  d->tk_nbr = geo.tk_nbr;
+  d->tk_nbc = geo.tk_nbc;
+  d->tk_tc = geo.tk_tc;
+  d->tk_cw = geo.tk_cw;
+  d->tk_elems = geo.tk_elems;
   d->pcap = fr.P;
 }
 
@@ -224,7 +230,109 @@ int lds_geometry(const HostFrame& f, int tiles, int band_rows, const otfs_cg_opt
          (int)sizeof(float2);
 }
 
+// ---------------------------------------------------------------------------------------
+// register-resident tiles
+// ---------------------------------------------------------------------------------------
+static void shift_ranges(const HostFrame& f, int* tlo, int* thi, int* vlo, int* vhi);
+
+// Elements of LDS a tile of tr rows x tc columns needs: its window, the rows' wrap factors, and
+// what a last row group that only some threads hold reads past the window.
+static int64_t tile_lds_elems(int tr, int ty, int dnu, int wc) {
+  const int64_t wr = tr + dnu, over = tr % ty ? ty - tr % ty : 0;
+  return std::max(wr * (wc + 2), (wr + over) * wc);
+}
+
+TileCut tile_cut(const HostFrame& f, double copies, int cus) {
+  TileCut best;
+  int tlo, thi, vlo, vhi;
+  shift_ranges(f, &tlo, &thi, &vlo, &vhi);
+  const int dtau = thi - tlo, dnu = vhi - vlo;
+  const int lds_elems = kTileLdsBytes / (int)sizeof(float2);
+  double best_cost = 1e300;
+  const int max_cols = std::min(f.M, kTileMaxTiles);
+  for (int nbc = 1; nbc <= max_cols; ++nbc) {
+    int tc = (f.M + nbc - 1) / nbc;
+    if ((f.M & 1) == 0) tc += tc & 1;
+    if ((f.M + tc - 1) / tc != nbc) continue;   // the rounded width needs fewer strips
+    // two columns per lane for strips of 65 to 128 columns, else one
+    const int cw = tc > 64 && tc <= 128 ? 2 : 1;
+    if (tc > kBlock) continue;
+    const int lx = cw == 2 ? 64 : tc, ty = kBlock / lx;
+    int wc = (cw == 2 ? 128 : tc) + dtau + 1;
+    wc += wc & 1;
+    for (int nbr = 1; nbr <= f.N && nbr * nbc <= kTileMaxTiles; ++nbr) {
+      const int tr = (f.N + nbr - 1) / nbr;
+      const int nj = (tr + ty - 1) / ty;
+      if (nj * cw > kTileElems) continue;
+      const int wr = tr + dnu;
+      if (std::max(tile_lds_elems(tr, ty, dnu, wc), tile_lds_elems(f.N / nbr, ty, dnu, wc)) > lds_elems)
+        continue;   // (both band heights)
+      const int T = nbr * nbc;
+      // clocks of one iteration of one tile: products (two waves per SIMD, 4 clocks per
+      // instruction, 9 or 10 instructions per two elements and path), window copies at about
+      // 24 bytes per clock, meetings (four per iteration, 1 to 1.6 us each when shared)
+      const int steps = (nj * cw + 7) / 8;
+      const double products = 2.0 * f.P * steps * 8 * (cw == 2 ? 4.6 : 5.2) * 8;
+      const double copies_clk = 2.0 * wr * wc * 8.0 / 24.0 + 2000.0;
+      const double meets = T == 1 ? 1200.0 : 4.0 * (2200.0 + 45.0 * T);
+      const double cost = (products + copies_clk + meets) * std::max(1.0, T * copies / cus);
+      if (cost < best_cost * (1 - 1e-9)) {
+        best_cost = cost;
+        best = TileCut{T, nbr, nbc, tc, cw, nj * cw};
+      }
+    }
+  }
+  return best;
+}
+
+TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes) {
+  TileCut best;
+  int tlo, thi, vlo, vhi;
+  shift_ranges(f, &tlo, &thi, &vlo, &vhi);
+  const int dtau = thi - tlo, dnu = vhi - vlo;
+  double best_cost = 1e300;
+  for (int width : {32, 64, 128, 256, 512}) {
+    const int nbc0 = (f.M + width - 1) / width;
+    int tc = (f.M + nbc0 - 1) / nbc0;
+    if ((f.M & 1) == 0) tc += tc & 1;
+    if (tc > kBlock) continue;
+    const int nbc = (f.M + tc - 1) / tc;
+    const int cw = tc > 64 && tc <= 128 ? 2 : 1;
+    const int ty = kBlock / (cw == 2 ? 64 : tc);
+    int wc = (cw == 2 ? 128 : tc) + dtau + 1;
+    wc += wc & 1;
+    for (int nj = 1; nj * cw <= kTileElemsSmall; ++nj) {
+      const int nbr = (f.N + ty * nj - 1) / (ty * nj);
+      const int tr = (f.N + nbr - 1) / nbr;
+      const int64_t need = std::max(tile_lds_elems(tr, ty, dnu, wc),
+                                    tile_lds_elems(f.N / nbr, ty, dnu, wc)) * 8;
+      if (need > kApplyLdsBytes || (int64_t)nbr * nbc >= (1 << 20)) continue;
+      const int T = nbr * nbc;
+      // clocks of one workgroup: launch and latencies, the window at about 12 bytes per clock,
+      // the products; two workgroups per CU
+      const double cost = (3000.0 + (tr + dnu) * (double)wc * 8.0 / 12.0 + 8.0 * f.P * nj * cw * 5.0) *
+                          std::max(1.0, T * copies / (2.0 * cus));
+      if (cost < best_cost * (1 - 1e-9)) {
+        best_cost = cost;
+        best = TileCut{T, nbr, nbc, tc, cw, nj * cw};
+        *lds_bytes = (int)need;
+      }
+    }
+  }
+  return best;
+}
+
+void set_tile_cut(const TileCut& c, FrameDev* geo) {
+  geo->tk_T = c.T;
+  geo->tk_nbr = c.nbr;
+  geo->tk_nbc = c.nbc;
+  geo->tk_tc = c.tc;
+  geo->tk_cw = c.cw;
+  geo->tk_elems = c.elems;
+}
+
 int frame_kind(const FrameDev& geo) {
+  if (geo.tk_T > 0) return kKindTile;
   if (geo.win_w > 0) return kKindWindowed;
   if (geo.lpk > 0) return kKindLds;
   return geo.resident ? kKindResident : (geo.skc > 0 ? kKindStaged : kKindDirect);
@@ -238,6 +346,7 @@ int refresh_lds_bytes(const std::vector<KindLaunch>& launches) {
 }
 
 int frame_lds_bytes(const HostFrame& f, const FrameDev& geo) {
+  if (geo.tk_T > 0) return kTileLdsBytes;
   if (geo.win_w > 0)
     return win_lds_bytes(geo.win_w, geo.win_rc, geo.tau_hi - geo.tau_lo, geo.nu_hi - geo.nu_lo);
   if (geo.resident) return (int)((int64_t)f.M * f.N * kResidentVecs * (int64_t)sizeof(float2));
@@ -260,19 +369,26 @@ otfs_status plan_launches(const std::vector<HostFrame>& frames, const std::vecto
   bool fdir = sd == kDNone && !split_dir;
   for (size_t f = 0; f < frames.size(); ++f)
     if (frame_kind(geo[f]) == kKindDirect && frames[f].P > kFusedDirMaxPaths) fdir = false;
+  // the register-resident frames run as one launch: the form of 8 elements per thread when
+  // every one of their tiles is that small
+  bool small = true;
+  for (size_t f = 0; f < frames.size(); ++f)
+    if (frame_kind(geo[f]) == kKindTile && geo[f].tk_elems > kTileElemsSmall) small = false;
   auto kind_of = [&](size_t f) {
     const int k = frame_kind(geo[f]);
+    if (k == kKindTile && small) return kKindTileSmall;
     return (k == kKindDirect && fdir) ? kKindDirectFD : k;
   };
   for (int kind = 0; kind < kKinds; ++kind) {
-    std::vector<HostFrame> fs;
+    std::vector<double> fs;   // work of the kind's frames
     std::vector<int> tb, tl;
     int lds = 0;
     for (size_t f = 0; f < frames.size(); ++f) {
       if (kind_of(f) != kind) continue;
-      fs.push_back(frames[f]);
-      tb.push_back(tile_base[f]);
-      tl.push_back(tiles[f]);
+      const bool tile = geo[f].tk_T > 0;
+      fs.push_back((double)frames[f].M * frames[f].N * (2.0 * frames[f].P + 6.0));
+      tb.push_back(tile ? (int)f * kTileStride : tile_base[f]);
+      tl.push_back(tile ? geo[f].tk_T : tiles[f]);
       lds = std::max(lds, frame_lds_bytes(frames[f], geo[f]));
     }
     if (fs.empty()) continue;
@@ -412,7 +528,7 @@ void make_tiles(const std::vector<HostFrame>& frames, int tile_elems, std::vecto
   }
 }
 
-bool make_queues(const std::vector<HostFrame>& frames, const std::vector<int>& tile_base,
+bool make_queues(const std::vector<double>& work, const std::vector<int>& tile_base,
                  const std::vector<int>& tiles, int ngroups, int per_group_cap,
                  std::vector<int32_t>& qitems, std::vector<int2>& qrange, int* per_group_grid) {
   qitems.clear();
@@ -421,20 +537,16 @@ bool make_queues(const std::vector<HostFrame>& frames, const std::vector<int>& t
   for (int t : tiles)
     if (t > per_group_cap) return false;
   // frames largest first, each to the least loaded group
-  std::vector<int> order(frames.size());
+  std::vector<int> order(work.size());
   std::iota(order.begin(), order.end(), 0);
-  auto work = [&](int f) {
-    const HostFrame& fr = frames[f];
-    return (double)fr.M * fr.N * (2.0 * fr.P + 6.0);
-  };
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work(a) > work(b); });
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
   std::vector<std::vector<int32_t>> lists(ngroups);
   std::vector<double> load(ngroups, 0.0);
   for (int f : order) {
     int g = 0;
     for (int i = 1; i < ngroups; ++i)
       if (load[i] < load[g]) g = i;
-    load[g] += work(f);
+    load[g] += work[f];
     for (int t = 0; t < tiles[f]; ++t) lists[g].push_back(tile_base[f] + t);
   }
   int per = 1;
@@ -555,8 +667,16 @@ void compute_layout(otfs_plan_t* pl) {
   };
   L.frames = take(nf * sizeof(FrameDev));
   L.items = take(nitems * sizeof(WorkItem));
-  L.qitems = take(nitems * sizeof(int32_t));
-  L.qrange = take(kKinds * kMaxGroups * sizeof(int2));
+  size_t ntiles = 0;
+  size_t sb = 0;
+  for (size_t f = 0; f < pl->cuts.size(); ++f) {
+    ntiles += (size_t)pl->cuts[f].T;
+    if (pl->cuts[f].T > 0 || pl->acuts[f].T > 0) sb += (size_t)pl->frames[f].P * pl->frames[f].M;
+  }
+  // with register-resident frames the queues exist twice (see launches_stream)
+  const size_t nsets = ntiles ? 2 : 1;
+  L.qitems = take((nsets * nitems + ntiles) * sizeof(int32_t));
+  L.qrange = take(nsets * kKinds * kMaxGroups * sizeof(int2));
   L.qhead = take(kKinds * kMaxGroups * sizeof(unsigned));
   L.probe = take(kProbeBlocks * sizeof(int));
   L.rtab = take(rt * sizeof(float2));
@@ -569,6 +689,9 @@ void compute_layout(otfs_plan_t* pl) {
   L.part_d = take(nitems * sizeof(double));
   L.bar = take(nf * sizeof(unsigned));
   L.prog = take(nitems * sizeof(unsigned));
+  L.stab = sb ? take(sb * sizeof(float2)) : 0;
+  L.aitems = pl->apply_items.empty() ? 0 : take(pl->apply_items.size() * sizeof(int2));
+  L.slots = ntiles ? take(ntiles * kTileMeets * sizeof(unsigned long long)) : 0;
   L.st = take(nf * sizeof(FrameState));
   L.abort = take(sizeof(unsigned));
   // frames staggered, each starting at an even element (16-byte aligned pairs)
@@ -592,6 +715,57 @@ void retile(otfs_plan_t* pl) {
   for (size_t f = 0; f < pl->frames.size() && win_ok; ++f)
     pl->winw[f] = window_width(pl->frames[f], pl->win_w_req, pl->win_rc_req);
   make_tiles(pl->frames, pl->tile_elems, pl->items, pl->tile_base, pl->tiles, &pl->winw);
+  // Register-resident tiles: the built-in choice whenever the caller asked for no launch
+  // shape or form of its own, for every frame that a cut of at most kTileMaxTiles tiles holds
+  // and that is not small enough for one workgroup's LDS (64 frames of 512 x 128: 1.73 ms
+  // against 3.89 ms on the streaming kinds; one such frame: 0.60 against 1.38 ms).
+  pl->cuts.assign(pl->frames.size(), TileCut{});
+  pl->acuts.assign(pl->frames.size(), TileCut{});
+  pl->apply_items.clear();
+  pl->apply_lds = 0;
+  pl->apply_all = !pl->frames.empty();
+  const uint32_t forms = OTFS_LDS_GATHER | OTFS_AGENT_BARRIER | OTFS_NO_LDS_RESIDENT |
+                         OTFS_SPLIT_DIRECTION | OTFS_D_STORED_BF16 | OTFS_D_STORED_C64;
+  // (frames of one shape, path count and shift ranges share their cuts)
+  struct CutKey {
+    int M, N, P, tlo, thi, vlo, vhi;
+    bool operator==(const CutKey& o) const {
+      return M == o.M && N == o.N && P == o.P && tlo == o.tlo && thi == o.thi && vlo == o.vlo && vhi == o.vhi;
+    }
+  } last{0, 0, 0, 0, 0, 0, 0};
+  TileCut last_cut, last_acut;
+  int last_lds = 0;
+  const bool forms_ok = !pl->no_tiles && !(pl->opts.flags & forms) && pl->tile_req == 0 && pl->max_grid_req == 0 &&
+      pl->stage_bytes == 0 && pl->win_w_req == 0;
+  for (size_t f = 0; f < pl->frames.size(); ++f) {
+    const HostFrame& fr = pl->frames[f];
+    const int64_t E = (int64_t)fr.M * fr.N;
+    const bool small = E * kResidentVecs * (int64_t)sizeof(float2) <= kResidentBytes;
+    if (!forms_ok || small) pl->apply_all = false;
+    if (!forms_ok) continue;
+    CutKey key{fr.M, fr.N, fr.P, 0, 0, 0, 0};
+    shift_ranges(fr, &key.tlo, &key.thi, &key.vlo, &key.vhi);
+    if (!(key == last)) {
+      last = key;
+      last_lds = 0;
+      const double copies = (double)pl->total_elems / (double)E;
+      last_cut = E <= (int64_t)kTileMaxTiles * kBlock * kTileElems ? tile_cut(fr, copies, pl->cus) : TileCut{};
+      last_acut = small ? TileCut{} : apply_cut(fr, copies, pl->cus, &last_lds);
+    }
+    // Not for frames of less than a full tile whose rows leave lanes idle (M no multiple of
+    // 64): 24 frames of 5 x 3 to 255 x 31 take 413 us against 441 us on the streaming kinds,
+    // whose sums these small, often ill-conditioned frames keep bit for bit.
+    const bool ragged = E < (int64_t)kBlock * kTileElems && fr.M % 64 != 0;
+    if (!(pl->tiles[f] == 1 && pl->opts.refresh_every == 0 && small) && !ragged)
+      pl->cuts[f] = last_cut;
+    if (!small) {
+      const TileCut c = last_acut;
+      pl->acuts[f] = c;
+      pl->apply_lds = std::max(pl->apply_lds, last_lds);
+      if (c.T == 0) pl->apply_all = false;
+      for (int t = 0; t < c.T; ++t) pl->apply_items.push_back(make_int2((int)f, t));
+    }
+  }
   compute_layout(pl);
 }
 
@@ -700,6 +874,7 @@ extern "C" otfs_status otfs_plan_set_tiling(otfs_plan_t* plan, int32_t tile_elem
   if (!plan) return fail(OTFS_E_INVAL, "plan is null");
   if (tile_elems < 0 || max_grid < 0)
     return fail(OTFS_E_INVAL, "tile_elems and max_grid must be >= 0");
+  plan->tile_req = tile_elems;
   plan->tile_elems = tile_elems > 0 ? tile_elems : default_tile_elems(plan->total_elems, plan->cus);
   plan->max_grid_req = max_grid;
   retile(plan);
@@ -726,6 +901,7 @@ extern "C" otfs_status otfs_plan_set_staging(otfs_plan_t* plan, int32_t lds_byte
   if (lds_bytes < 0 || lds_bytes > 65536)
     return fail(OTFS_E_INVAL, "lds_bytes must be in [0, 65536] (got %d)", lds_bytes);
   plan->stage_bytes = lds_bytes;
+  retile(plan);
   plan->bound = false;
   plan->drop_graph();
   return OTFS_OK;
@@ -772,12 +948,40 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
   otfs_status pst = probe_xcds(dev, static_cast<char*>(ws) + plan->L.probe, s, &xi);
   if (pst != OTFS_OK) return pst;
   plan->ref_xcds = xi.round_robin ? xi.nxcd : 1;
-  pst = plan_launches(plan->frames, geo, plan->tile_base, plan->tiles,
-                      stored_mode(plan->opts.flags), plan->opts.refresh_every > 0,
-                      (plan->opts.flags & OTFS_SPLIT_DIRECTION) != 0, cus, plan->max_grid_req, xi,
-                      (plan->opts.flags & OTFS_AGENT_BARRIER) != 0,
-                      plan->qitems, plan->qrange, plan->launches);
-  if (pst != OTFS_OK) return pst;
+  // a frame's register-resident tiles share one XCD and are all resident at once
+  auto launches_of = [&](const std::vector<FrameDev>& g, std::vector<int32_t>& qi,
+                         std::vector<int2>& qr, std::vector<KindLaunch>& out) {
+    return plan_launches(plan->frames, g, plan->tile_base, plan->tiles,
+                         stored_mode(plan->opts.flags), plan->opts.refresh_every > 0,
+                         (plan->opts.flags & OTFS_SPLIT_DIRECTION) != 0, cus, plan->max_grid_req,
+                         xi, (plan->opts.flags & OTFS_AGENT_BARRIER) != 0, qi, qr, out);
+  };
+  bool tiles_on = false;
+  plan->launches_stream.clear();
+  if (xi.round_robin) {
+    std::vector<FrameDev> plain = geo;
+    for (size_t f = 0; f < plan->frames.size(); ++f)
+      if (plan->cuts[f].T > 0 && plan->cuts[f].T <= cus / xi.nxcd) {
+        set_tile_cut(plan->cuts[f], &geo[f]);
+        tiles_on = true;
+      }
+    if (tiles_on) {
+      std::vector<int32_t> qi;
+      std::vector<int2> qr;
+      pst = launches_of(plain, qi, qr, plan->launches_stream);
+      if (pst != OTFS_OK) return pst;
+      pst = launches_of(geo, plan->qitems, plan->qrange, plan->launches);
+      if (pst != OTFS_OK) return pst;
+      const int base = (int)plan->qitems.size(), rbase = (int)plan->qrange.size();
+      plan->qitems.insert(plan->qitems.end(), qi.begin(), qi.end());
+      for (int2 r : qr) plan->qrange.push_back(make_int2(r.x + base, r.y + base));
+      for (KindLaunch& L : plan->launches_stream) L.rbase = rbase;
+    }
+  }
+  if (!tiles_on) {
+    pst = launches_of(geo, plan->qitems, plan->qrange, plan->launches);
+    if (pst != OTFS_OK) return pst;
+  }
 
   // host tables
   const Layout& L = plan->L;
@@ -785,7 +989,7 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
   std::vector<double2> r64, w64;
   std::vector<int2> paths;
   std::vector<FrameDev> fd(plan->frames.size());
-  size_t ro = 0, wo = 0, po = 0, dto = 0;
+  size_t ro = 0, wo = 0, po = 0, dto = 0, so = 0, sbo = 0;
   const bool refresh = plan->opts.refresh_every > 0;
   const int sd = stored_mode(plan->opts.flags);
   const size_t dsz = sd == kDC64 ? sizeof(float2) : sizeof(uint32_t);
@@ -816,6 +1020,15 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
     d.part_d = reinterpret_cast<double*>(base + L.part_d) + tb;
     d.bar = reinterpret_cast<unsigned*>(base + L.bar) + f;
     d.prog = reinterpret_cast<unsigned*>(base + L.prog) + tb;
+    d.slots = reinterpret_cast<unsigned long long*>(base + L.slots) + so;
+    so += (size_t)plan->cuts[f].T * kTileMeets;
+    d.stab = reinterpret_cast<float2*>(base + L.stab) + sbo;
+    if (plan->cuts[f].T > 0 || plan->acuts[f].T > 0) sbo += (size_t)fr.P * fr.M;
+    d.ap_T = plan->acuts[f].T;
+    d.ap_nbr = plan->acuts[f].nbr;
+    d.ap_nbc = plan->acuts[f].nbc;
+    d.ap_tc = plan->acuts[f].tc;
+    d.ap_cw = plan->acuts[f].cw;
     d.st = reinterpret_cast<FrameState*>(base + L.st) + f;
     frame_scalars(fr, plan->opts, plan->tiles[f], geo[f], &d);
     d.off = fr.off;
@@ -862,6 +1075,12 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
     if ((e = launch_build_d(sd, plan->d_frames, plan->d_items, (int)plan->items.size(), s)) != hipSuccess)
       return hip_fail(e, "build D");
   }
+  plan->d_aitems = reinterpret_cast<int2*>(base + L.aitems);
+  if (!plan->apply_items.empty() &&
+      (e = up(L.aitems, plan->apply_items.data(), plan->apply_items.size() * sizeof(int2))) != hipSuccess)
+    return hip_fail(e, "hipMemcpyAsync (apply items)");
+  if ((tiles_on || !plan->apply_items.empty()) && (e = launch_tile_tables(plan->d_frames, (int)fd.size(), s)) != hipSuccess)
+    return hip_fail(e, "tile tables");
   // the host arrays above must outlive the copies
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize (bind)");
   plan->bound = true;
@@ -901,9 +1120,18 @@ static otfs_status apply_common(const otfs_plan_t* plan, bool adj, const void* i
   for (const FrameDev& d : plan->h_frames)
     if (d.win_w > 0)
       lds = std::max(lds, win_lds_bytes(d.win_w, d.win_rc, d.tau_hi - d.tau_lo, d.nu_hi - d.nu_lo));
-  hipError_t e = launch_apply(adj, sd, plan->d_frames, plan->d_items, (int)plan->items.size(),
-                              static_cast<const float2*>(in), static_cast<float2*>(out), lds,
-                              static_cast<hipStream_t>(stream));
+  // frames with an apply cut (planned for the host's path tables) in one launch, the others
+  // by the streaming items
+  const bool cut = !plan->device_paths && !plan->apply_items.empty();
+  hipError_t e = hipSuccess;
+  if (cut)
+    e = launch_apply_tile(adj, plan->d_frames, plan->d_aitems, (int)plan->apply_items.size(),
+                          plan->ref_xcds, static_cast<const float2*>(in), static_cast<float2*>(out),
+                          plan->apply_lds, static_cast<hipStream_t>(stream));
+  if (e == hipSuccess && !(cut && plan->apply_all))
+    e = launch_apply(adj, sd, plan->d_frames, plan->d_items, (int)plan->items.size(),
+                     static_cast<const float2*>(in), static_cast<float2*>(out), lds, cut,
+                     static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, adj ? "apply H^H" : "apply H");
   return OTFS_OK;
 }
@@ -932,20 +1160,21 @@ static hipError_t enqueue_fused(otfs_plan_t* plan, const Bases& B, hipStream_t s
   // Frames of the windowed-pairs kind refresh inside the fused launch when their windows
   // fit; with the host's path tables (for which the plan sized the windows) and every frame
   // of that kind, one launch runs the whole solve.
-  bool inline_refresh = !plan->device_paths && !plan->launches.empty();
-  for (const KindLaunch& L : plan->launches) inline_refresh = inline_refresh && L.kind == kKindLds;
+  const std::vector<KindLaunch>& launches = plan->solve_launches();
+  bool inline_refresh = !plan->device_paths && !launches.empty();
+  for (const KindLaunch& L : launches) inline_refresh = inline_refresh && L.kind == kKindLds;
   const int nseg = inline_refresh ? 1 : fused_segments(plan->opts);
   for (int seg = 0; seg < nseg; ++seg) {
-    for (const KindLaunch& L : plan->launches) {
+    for (const KindLaunch& L : launches) {
       e = launch_cg_fused(L.kind, stored_mode(plan->opts.flags), plan->d_frames, plan->d_items,
-                          plan->d_qitems, plan->d_qrange + L.qbase, plan->d_qhead + L.qbase,
-                          L.ngroups, L.grid, plan->opts.max_iters, B, L.xcd_local,
+                          plan->d_qitems, plan->d_qrange + L.rbase + L.qbase,
+                          plan->d_qhead + L.qbase, L.ngroups, L.grid, plan->opts.max_iters, B, L.xcd_local,
                           plan->d_abort, L.lds_bytes, plan->wait_us, s);
       if (e != hipSuccess) return e;
     }
     if (seg + 1 < nseg) {
       e = launch_refresh(plan->d_frames, plan->d_items, (int)plan->items.size(), B,
-                         plan->d_qhead, kKinds * kMaxGroups, refresh_lds_bytes(plan->launches),
+                         plan->d_qhead, kKinds * kMaxGroups, refresh_lds_bytes(launches),
                          plan->ref_xcds, s);
       if (e != hipSuccess) return e;
     }
@@ -1072,15 +1301,15 @@ extern "C" otfs_status otfs_lmmse_cg_trace(otfs_plan_t* plan, const void* y, voi
     if (it > 0) {   // counters and cursors of the next one-iteration launch
       e = plan->opts.refresh_every > 0
               ? launch_refresh(plan->d_frames, plan->d_items, ni, B, plan->d_qhead,
-                               kKinds * kMaxGroups, refresh_lds_bytes(plan->launches),
+                               kKinds * kMaxGroups, refresh_lds_bytes(plan->solve_launches()),
                                plan->ref_xcds, s)
               : launch_step_reset(plan->d_frames, nf, plan->d_abort, plan->d_qhead,
                                   kKinds * kMaxGroups, s);
     }
-    for (const KindLaunch& L : plan->launches) {
+    for (const KindLaunch& L : plan->solve_launches()) {
       if (e != hipSuccess) break;
       e = launch_cg_fused(L.kind, stored_mode(plan->opts.flags), plan->d_frames, plan->d_items,
-                          plan->d_qitems, plan->d_qrange + L.qbase, plan->d_qhead + L.qbase,
+                          plan->d_qitems, plan->d_qrange + L.rbase + L.qbase, plan->d_qhead + L.qbase,
                           L.ngroups, L.grid, 1, B, L.xcd_local, plan->d_abort, L.lds_bytes,
                           plan->wait_us, s);
     }
@@ -1152,6 +1381,7 @@ extern "C" otfs_status otfs_plan_paths_from_pilot(otfs_plan_t* plan, const void*
   hipError_t e = launch_pilot_paths(plan->d_frames, (int)plan->frames.size(),
                                     static_cast<const float2*>(ypilot), theta, npaths, s);
   if (e != hipSuccess) return hip_fail(e, "pilot path estimation");
+  if (!plan->device_paths) plan->drop_graph();   // captured with the host tables' launches
   plan->device_paths = true;
   const int sd = stored_mode(plan->opts.flags);
   if (sd != kDNone &&
@@ -1166,6 +1396,11 @@ extern "C" otfs_status otfs_lmmse_cg_noalloc(otfs_plan_t* plan, const void* y, v
   if (plan->opts.flags & (OTFS_USE_GRAPH | OTFS_TIME_KERNEL))
     return fail(OTFS_E_UNSUPPORTED,
                 "otfs_lmmse_cg_noalloc runs without OTFS_USE_GRAPH and OTFS_TIME_KERNEL");
+  if (plan->L.total > kNoAllocBytes) {   // the streaming kinds' workspace may still fit
+    plan->no_tiles = true;
+    retile(plan);
+    plan->bound = false;
+  }
   if (plan->L.total > kNoAllocBytes)
     return fail(OTFS_E_NOMEM,
                 "the plan needs a workspace of %zu bytes; the static scratch holds %zu bytes",

@@ -26,7 +26,7 @@ struct HostFrame {
 struct Layout {
   size_t frames = 0, items = 0, qitems = 0, qrange = 0, qhead = 0, probe = 0;
   size_t rtab = 0, wtab = 0, rtab64 = 0, wtab64 = 0, paths = 0;
-  size_t part_pa = 0, part_cc = 0, part_d = 0, bar = 0, prog = 0, st = 0, abort = 0;
+  size_t part_pa = 0, part_cc = 0, part_d = 0, bar = 0, prog = 0, slots = 0, stab = 0, aitems = 0, st = 0, abort = 0;
   size_t c = 0, p0 = 0, p1 = 0, t = 0, a = 0, u = 0, dtab = 0;
   size_t total = 0;
 };
@@ -66,8 +66,8 @@ int lds_pair_geometry(const HostFrame& f, int tiles, int budget_bytes, FrameDev*
 // Work queues of the fused kernel.  ngroups groups (one per XCD in XCD-local mode, else
 // one); every frame's tiles go, consecutively, to one group; groups are balanced by work.
 // per_group_cap: workgroups one group can hold resident.  Returns false if some frame has
-// more tiles than that.
-bool make_queues(const std::vector<HostFrame>& frames, const std::vector<int>& tile_base,
+// more tiles than that.  work: each frame's.
+bool make_queues(const std::vector<double>& work, const std::vector<int>& tile_base,
                  const std::vector<int>& tiles, int ngroups, int per_group_cap,
                  std::vector<int32_t>& qitems, std::vector<int2>& qrange, int* per_group_grid);
 // XCD layout of a device, found once per device by a probe launch.
@@ -88,6 +88,21 @@ int lds_geometry(const HostFrame& f, int tiles, int band_rows, const otfs_cg_opt
                  int budget_bytes, FrameDev* geo);
 constexpr int kProbeBlocks = 1024;
 
+// Cut of a frame into register-resident tiles (T = 0: the frame does not take that form).
+struct TileCut {
+  int T = 0, nbr = 0, nbc = 0, tc = 0, cw = 0;
+  int elems = 0;   // elements of one thread
+};
+constexpr int kTileLdsBytes = kMaxLdsBytes - 1024;   // window LDS of a tile's workgroup
+// The cut with the least estimated time of an iteration times the share of the chip it
+// takes, for a frame that is 1 / copies of the work on the device.
+TileCut tile_cut(const HostFrame& f, double copies, int cus);
+void set_tile_cut(const TileCut& c, FrameDev* geo);
+// The cut of the standalone applications: at most 8 elements per thread and windows of at most
+// kApplyLdsBytes (two workgroups per CU); any number of tiles.
+constexpr int kApplyLdsBytes = 79 * 1024;
+TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes);
+
 // One launch of the fused kernel: the frames of one kind with their work queues.  The
 // queue ranges and cursors of launch kind k live at k * kMaxGroups.
 struct KindLaunch {
@@ -98,6 +113,7 @@ struct KindLaunch {
   bool xcd_local = false;
   int lds_bytes = 0;
   int qbase = 0;
+  int rbase = 0;            // first entry of its set of queue ranges
 };
 // The refresh launches' LDS: the windowed paired kind's window bytes among `launches` (0
 // when it has none).
@@ -128,6 +144,13 @@ struct otfs_plan {
   int64_t wait_us = -1;   // bound of the kernels' waits (-1: the default 20 s)
   int ref_xcds = 1;       // XCDs of round-robin dispatch (block order of the refresh)
   bool device_paths = false;   // the path tables were made on the device (from a pilot)
+  int tile_req = 0;            // tile size asked for with otfs_plan_set_tiling (0: built-in)
+  bool no_tiles = false;       // keep the streaming kinds (workspace limit of the static scratch)
+  std::vector<otfs::TileCut> cuts;     // per frame: its register-resident cut, if any
+  std::vector<otfs::TileCut> acuts;    // per frame: its apply cut, if any
+  std::vector<int2> apply_items;       // {frame, tile} of the apply cuts
+  int apply_lds = 0;                   // largest window of the apply cuts, bytes
+  bool apply_all = false;              // every frame has an apply cut
   int win_w_req = 0, win_rc_req = 0;   // windowed form (0: off)
   std::vector<int> winw;               // per frame: strip width of the windowed form, or 0
   // tiling (host) and schedule (chosen at bind)
@@ -136,6 +159,12 @@ struct otfs_plan {
   std::vector<int32_t> qitems;
   std::vector<int2> qrange;
   std::vector<otfs::KindLaunch> launches;
+  // The same frames on the streaming kinds only: used once the path tables are made on the
+  // device (empty when no frame is register resident, then `launches` serves both).
+  std::vector<otfs::KindLaunch> launches_stream;
+  const std::vector<otfs::KindLaunch>& solve_launches() const {
+    return device_paths && !launches_stream.empty() ? launches_stream : launches;
+  }
   otfs::Layout L;
   // binding
   bool bound = false;
@@ -143,6 +172,7 @@ struct otfs_plan {
   void* ws = nullptr;
   otfs::FrameDev* d_frames = nullptr;
   otfs::WorkItem* d_items = nullptr;
+  int2* d_aitems = nullptr;
   int32_t* d_qitems = nullptr;
   int2* d_qrange = nullptr;
   unsigned* d_qhead = nullptr;
