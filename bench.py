@@ -297,12 +297,11 @@ def plain_block(otfs, O, np, torch, frames, ys, refs, refresh, offs, reps=3):
             "note": "no FP64 refresh in the plain form" if refresh else ""}
 
 
-PEAK_MFMA_FP32_TFLOPS = 157.3
 
 
 def dzt_block(otfs, np, torch, M, N, nframes, reps=10):
-    """The front end's DZT (Eq. zak as the batched GEMM of Eq. zak_gemm on FP32 MFMA) of a
-    batch of time-domain frames: 8 M N^2 real flops per frame, timed with HIP events."""
+    """The front end's DZT (Eq. zak) of a batch of time-domain frames, by passes of short DFTs:
+    16 M N bytes per frame, timed with HIP events."""
     x = torch.randn(nframes * M * N, dtype=torch.complex64, device="cuda")
     out = torch.empty_like(x)
     otfs.dzt(x, M, N, out=out)
@@ -316,14 +315,12 @@ def dzt_block(otfs, np, torch, M, N, nframes, reps=10):
         torch.cuda.synchronize()
         ts.append(e0.elapsed_time(e1))
     ms = float(np.median(ts))
-    flops = 8.0 * M * N * N * nframes
+    gbs = 16.0 * M * N * nframes / (ms * 1e-3) / 1e9
     del x, out
     return {"workload": f"{nframes} x ({M},{N}) time-domain frames", "ms": ms,
             "frames_per_s": nframes / (ms * 1e-3),
-            "roofline": {"bound": "mfma", "achieved": flops / (ms * 1e-3) / 1e12,
-                         "peak": PEAK_MFMA_FP32_TFLOPS, "unit": "TFLOP/s",
-                         "frac": flops / (ms * 1e-3) / 1e12 / PEAK_MFMA_FP32_TFLOPS,
-                         "kernel": "k_dzt (v_mfma_f32_16x16x4_f32)"}}
+            "roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                         "frac": gbs / PEAK_HBM_GBS, "kernel": "k_dzt_fft"}}
 
 
 def plan_elems(specs):

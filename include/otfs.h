@@ -253,9 +253,10 @@ otfs_status otfs_lmmse_cg_plain(otfs_plan_t* plan, const void* y_dev, void* xhat
 /* ------------------------------------------------------------------------------------ */
 /* DZT of nframes received time-domain frames (Sec. III-A, Eq. zak):
  *     Y[k, l] = N^{-1/2} sum_{i=0}^{N-1} y[k + i M] e^{-j 2 pi i l / N},
- * computed as the batched complex GEMM of Sec. IV-A (Eq. zak_gemm): per frame the N x M
+ * the batched complex product of Sec. IV-A (Eq. zak_gemm): per frame the N x M
  * matrix of samples (row i = slot, column k = delay) is multiplied by the N x N kernel
- * e^{-j 2 pi l i / N} / sqrt(N) on the matrix cores (FP32 MFMA, FP32 accumulation).  The
+ * e^{-j 2 pi l i / N} / sqrt(N): by passes of short DFTs in FP32 for 65 to 2048 bins that
+ * split into two or three factors of at most 16, else on the matrix cores (FP32 MFMA).  The
  * kernel is the unitary one of Eq. zak; the printed kernel matrix of Eq. zak_exp differs
  * from it by the factor sqrt(N) (-1)^l.  inverse != 0 computes Eq. iZak instead.
  * in_dev: nframes * M * N complex64, frame after frame, sample i*M + k; out_dev: the same

@@ -280,7 +280,8 @@ hipError_t launch_gather_segments(const CopySeg* segs, int nseg, unsigned char* 
                                   hipStream_t s);
 
 // Discrete Zak transform (inverse = false, Eq. zak) or its inverse (Eq. iZak) of nframes
-// frames of M x N complex64 samples (dzt.hip): batched GEMM on MFMA.  in and out distinct.
+// frames of M x N complex64 samples (dzt.hip): passes of short DFTs or a batched GEMM
+// on MFMA.  in and out distinct.
 hipError_t launch_dzt(int M, int N, int nframes, bool inverse, const float2* in, float2* out,
                       hipStream_t s);
 constexpr int kDztMaxN = 8192;   // twiddle table of N complex64 values in LDS (64 KiB)

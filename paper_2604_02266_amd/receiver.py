@@ -1,7 +1,7 @@
 """The Zak-OTFS receiver chain on the device (Sec. III-A pipeline, Fig. otfs_pipeline):
 
   received pilot and data frames (time domain)
-    -> DZT of every frame (Eq. zak, the batched GEMM of Eq. zak_gemm on MFMA; otfs_dzt)
+    -> DZT of every frame (Eq. zak, the batched product of Eq. zak_gemm; otfs_dzt)
     -> the channel's dominant paths from the pilot (Eqs. heff_hadamard, heff_thres;
        otfs_plan_paths_from_pilot), without a host round trip
     -> LMMSE-CG equalisation of the data frames (Algorithm 1; otfs_lmmse_cg)
