@@ -7,6 +7,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <numeric>
 #include <queue>
 #include <string>
@@ -104,6 +106,10 @@ otfs_status validate_frame(const otfs_frame_desc& f, int idx, HostFrame* out) {
   std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
     return h.nu[a] != h.nu[b] ? h.nu[a] < h.nu[b] : h.tau[a] < h.tau[b];
   });
+  if (std::is_sorted(ord.begin(), ord.end())) {
+    *out = std::move(h);
+    return OTFS_OK;
+  }
   HostFrame g = h;
   for (int p = 0; p < h.P; ++p) {
     g.tau[p] = h.tau[ord[p]];
@@ -114,15 +120,17 @@ otfs_status validate_frame(const otfs_frame_desc& f, int idx, HostFrame* out) {
   return OTFS_OK;
 }
 
-// R_p[k] = h_p e^{j 2 pi nu_p (k - tau_p) / (MN)} for k in [0, M).  With k = 32 kh + kl the
-// phase splits into a block part nu_p (32 kh - tau_p) and an in-block part nu_p kl; each
-// numerator is reduced modulo MN in exact integer arithmetic before its angle is formed in
-// FP64, and R_p[k] is h_p times the product of the two unit phasors (about 2 sqrt(M)
-// sine/cosine evaluations instead of 2 M; the product adds a few FP64 roundings).
-void delay_ramp(const HostFrame& f, int p, std::vector<double2>& out) {
+// R_p[k] = h_p e^{j 2 pi nu_p (k - tau_p) / (MN)} for k in [0, M), path after path, and W[l] =
+// e^{j 2 pi l / N}.  With k = 32 kh + kl the phase splits into a block part
+// nu_p (32 kh - tau_p) and an in-block part nu_p kl; each numerator is reduced modulo MN in
+// exact integer arithmetic before its angle is formed in FP64, and R_p[k] is h_p times the
+// product of the two unit phasors (about 2 sqrt(M) sine/cosine evaluations instead of 2 M; the
+// product adds a few FP64 roundings).  The in-block phasors of consecutive paths of one Doppler
+// bin (the paths are sorted by it) are formed once; a path of Doppler 0 is one value.  The FP32
+// tables are those numbers rounded; the FP64 ones are written where asked for.
+void frame_tables(const HostFrame& f, float2* r32, float2* w32, double2* r64, double2* w64) {
   constexpr int kB = 32;
   const int64_t MN = (int64_t)f.M * f.N;
-  const int64_t nu = f.nu[p];
   auto phasor = [&](int64_t num) {
     num %= MN;
     if (num < 0) num += MN;
@@ -130,16 +138,36 @@ void delay_ramp(const HostFrame& f, int p, std::vector<double2>& out) {
     return make_double2(std::cos(ang), std::sin(ang));
   };
   const int nl = f.M < kB ? f.M : kB;
-  std::vector<double2> lo(nl);
-  for (int kl = 0; kl < nl; ++kl) lo[kl] = phasor(nu * kl);
-  const double hr = f.h[p].x, hi = f.h[p].y;
-  for (int kh = 0; kh * kB < f.M; ++kh) {
-    const double2 b = phasor(nu * ((int64_t)kh * kB - f.tau[p]));
-    for (int kl = 0; kl < kB && kh * kB + kl < f.M; ++kl) {
-      const double c = b.x * lo[kl].x - b.y * lo[kl].y;
-      const double s = b.x * lo[kl].y + b.y * lo[kl].x;
-      out.push_back(make_double2(hr * c - hi * s, hr * s + hi * c));
+  double2 lo[kB];
+  for (int p = 0; p < f.P; ++p) {
+    const int64_t nu = f.nu[p];
+    const double hr = f.h[p].x, hi = f.h[p].y;
+    const size_t at = (size_t)p * f.M;
+    if (nu == 0) {   // both phasors are 1
+      const double2 v = make_double2(hr * 1.0 - hi * 0.0, hr * 0.0 + hi * 1.0);
+      std::fill(r32 + at, r32 + at + f.M, make_float2((float)v.x, (float)v.y));
+      if (r64) std::fill(r64 + at, r64 + at + f.M, v);
+      continue;
     }
+    if (p == 0 || f.nu[p - 1] != nu)
+      for (int kl = 0; kl < nl; ++kl) lo[kl] = phasor(nu * kl);
+    for (int k0 = 0; k0 < f.M; k0 += kB) {
+      const double2 b = phasor(nu * ((int64_t)k0 - f.tau[p]));
+      const int n = std::min(kB, f.M - k0);
+      for (int kl = 0; kl < n; ++kl) {
+        const double c = b.x * lo[kl].x - b.y * lo[kl].y;
+        const double s = b.x * lo[kl].y + b.y * lo[kl].x;
+        const double2 v = make_double2(hr * c - hi * s, hr * s + hi * c);
+        r32[at + k0 + kl] = make_float2((float)v.x, (float)v.y);
+        if (r64) r64[at + k0 + kl] = v;
+      }
+    }
+  }
+  for (int l = 0; l < f.N; ++l) {
+    const double ang = 2.0 * M_PI * ((double)l / (double)f.N);
+    const double2 v = make_double2(std::cos(ang), std::sin(ang));
+    w32[l] = make_float2((float)v.x, (float)v.y);
+    if (w64) w64[l] = v;
   }
 }
 
@@ -425,14 +453,6 @@ otfs_status plan_launches(const std::vector<HostFrame>& frames, const std::vecto
   return OTFS_OK;
 }
 
-// W[l] = e^{j 2 pi l / N}
-void wrap_factors(const HostFrame& f, std::vector<double2>& out) {
-  for (int l = 0; l < f.N; ++l) {
-    const double ang = 2.0 * M_PI * ((double)l / (double)f.N);
-    out.push_back(make_double2(std::cos(ang), std::sin(ang)));
-  }
-}
-
 // ---------------------------------------------------------------------------------------
 // tiling: frame f is split into T_f bands of Doppler rows, one workgroup each
 // ---------------------------------------------------------------------------------------
@@ -677,20 +697,21 @@ void compute_layout(otfs_plan_t* pl) {
   const size_t nsets = ntiles ? 2 : 1;
   L.qitems = take((nsets * nitems + ntiles) * sizeof(int32_t));
   L.qrange = take(nsets * kKinds * kMaxGroups * sizeof(int2));
-  L.qhead = take(kKinds * kMaxGroups * sizeof(unsigned));
-  L.probe = take(kProbeBlocks * sizeof(int));
   L.rtab = take(rt * sizeof(float2));
   L.wtab = take(wt * sizeof(float2));
   L.rtab64 = refresh ? take(rt * sizeof(double2)) : 0;
   L.wtab64 = refresh ? take(wt * sizeof(double2)) : 0;
   L.paths = take(np * sizeof(int2));
+  L.aitems = pl->apply_items.empty() ? 0 : take(pl->apply_items.size() * sizeof(int2));
+  L.uploaded = o;
+  L.qhead = take(kKinds * kMaxGroups * sizeof(unsigned));
+  L.probe = take(kProbeBlocks * sizeof(int));
   L.part_pa = take(nitems * sizeof(float));
   L.part_cc = take(nitems * sizeof(float));
   L.part_d = take(nitems * sizeof(double));
   L.bar = take(nf * sizeof(unsigned));
   L.prog = take(nitems * sizeof(unsigned));
   L.stab = sb ? take(sb * sizeof(float2)) : 0;
-  L.aitems = pl->apply_items.empty() ? 0 : take(pl->apply_items.size() * sizeof(int2));
   L.slots = ntiles ? take(ntiles * kTileMeets * sizeof(unsigned long long)) : 0;
   L.st = take(nf * sizeof(FrameState));
   L.abort = take(sizeof(unsigned));
@@ -986,8 +1007,10 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
   // host tables
   const Layout& L = plan->L;
   char* base = static_cast<char*>(ws);
-  std::vector<double2> r64, w64;
-  std::vector<int2> paths;
+  // the uploaded regions as they lie in the workspace: one copy
+  std::unique_ptr<char[]> host(new (std::nothrow) char[L.uploaded]);
+  if (!host) return fail(OTFS_E_NOMEM, "out of host memory");
+  auto at = [&](size_t off) { return host.get() + off; };
   std::vector<FrameDev> fd(plan->frames.size());
   size_t ro = 0, wo = 0, po = 0, dto = 0, so = 0, sbo = 0;
   const bool refresh = plan->opts.refresh_every > 0;
@@ -997,9 +1020,11 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
     const HostFrame& fr = plan->frames[f];
     FrameDev& d = fd[f];
     std::memset(&d, 0, sizeof d);
-    for (int p = 0; p < fr.P; ++p) delay_ramp(fr, p, r64);
-    wrap_factors(fr, w64);
-    for (int p = 0; p < fr.P; ++p) paths.push_back(make_int2(fr.tau[p], fr.nu[p]));
+    frame_tables(fr, reinterpret_cast<float2*>(at(L.rtab)) + ro, reinterpret_cast<float2*>(at(L.wtab)) + wo,
+                 refresh ? reinterpret_cast<double2*>(at(L.rtab64)) + ro : nullptr,
+                 refresh ? reinterpret_cast<double2*>(at(L.wtab64)) + wo : nullptr);
+    int2* const paths = reinterpret_cast<int2*>(at(L.paths)) + po;
+    for (int p = 0; p < fr.P; ++p) paths[p] = make_int2(fr.tau[p], fr.nu[p]);
     const size_t E = (size_t)fr.M * fr.N;
     const size_t eo = frame_vec_offset(fr.off, f);
     d.c = reinterpret_cast<float2*>(base + L.c) + eo;
@@ -1038,32 +1063,18 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
     po += (size_t)fr.P;
     dto += (size_t)fr.P * E;
   }
-  plan->h_rtab.resize(r64.size());
-  plan->h_wtab.resize(w64.size());
-  for (size_t i = 0; i < r64.size(); ++i) plan->h_rtab[i] = make_float2((float)r64[i].x, (float)r64[i].y);
-  for (size_t i = 0; i < w64.size(); ++i) plan->h_wtab[i] = make_float2((float)w64[i].x, (float)w64[i].y);
-  plan->h_rtab64 = refresh ? r64 : std::vector<double2>();
-  plan->h_wtab64 = refresh ? w64 : std::vector<double2>();
-  plan->h_paths = paths;
-  plan->h_frames = fd;
-
-  auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
-    if (bytes == 0) return hipSuccess;
-    return hipMemcpyAsync(base + off, src, bytes, hipMemcpyHostToDevice, s);
+  auto put = [&](size_t off, const void* src, size_t bytes) {
+    if (bytes) std::memcpy(at(off), src, bytes);
   };
-  if ((e = up(L.frames, fd.data(), fd.size() * sizeof(FrameDev))) != hipSuccess ||
-      (e = up(L.items, plan->items.data(), plan->items.size() * sizeof(WorkItem))) != hipSuccess ||
-      (e = up(L.qitems, plan->qitems.data(), plan->qitems.size() * sizeof(int32_t))) != hipSuccess ||
-      (e = up(L.qrange, plan->qrange.data(), plan->qrange.size() * sizeof(int2))) != hipSuccess ||
-      (e = up(L.rtab, plan->h_rtab.data(), plan->h_rtab.size() * sizeof(float2))) != hipSuccess ||
-      (e = up(L.wtab, plan->h_wtab.data(), plan->h_wtab.size() * sizeof(float2))) != hipSuccess ||
-      (e = up(L.paths, plan->h_paths.data(), plan->h_paths.size() * sizeof(int2))) != hipSuccess)
+  put(L.frames, fd.data(), fd.size() * sizeof(FrameDev));
+  put(L.items, plan->items.data(), plan->items.size() * sizeof(WorkItem));
+  put(L.qitems, plan->qitems.data(), plan->qitems.size() * sizeof(int32_t));
+  put(L.qrange, plan->qrange.data(), plan->qrange.size() * sizeof(int2));
+  put(L.aitems, plan->apply_items.data(), plan->apply_items.size() * sizeof(int2));
+  plan->h_frames = std::move(fd);
+  if (L.uploaded > 0 &&
+      (e = hipMemcpyAsync(base, host.get(), L.uploaded, hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_fail(e, "hipMemcpyAsync (plan tables)");
-  if (refresh) {
-    if ((e = up(L.rtab64, plan->h_rtab64.data(), plan->h_rtab64.size() * sizeof(double2))) != hipSuccess ||
-        (e = up(L.wtab64, plan->h_wtab64.data(), plan->h_wtab64.size() * sizeof(double2))) != hipSuccess)
-      return hip_fail(e, "hipMemcpyAsync (FP64 tables)");
-  }
   plan->ws = ws;
   plan->d_frames = reinterpret_cast<FrameDev*>(base + L.frames);
   plan->d_items = reinterpret_cast<WorkItem*>(base + L.items);
@@ -1076,12 +1087,9 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
       return hip_fail(e, "build D");
   }
   plan->d_aitems = reinterpret_cast<int2*>(base + L.aitems);
-  if (!plan->apply_items.empty() &&
-      (e = up(L.aitems, plan->apply_items.data(), plan->apply_items.size() * sizeof(int2))) != hipSuccess)
-    return hip_fail(e, "hipMemcpyAsync (apply items)");
-  if ((tiles_on || !plan->apply_items.empty()) && (e = launch_tile_tables(plan->d_frames, (int)fd.size(), s)) != hipSuccess)
+  if ((tiles_on || !plan->apply_items.empty()) && (e = launch_tile_tables(plan->d_frames, (int)plan->frames.size(), s)) != hipSuccess)
     return hip_fail(e, "tile tables");
-  // the host arrays above must outlive the copies
+  // the host copy must outlive the transfer
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize (bind)");
   plan->bound = true;
   plan->device_paths = false;   // the tables just uploaded are the host's

@@ -28,6 +28,7 @@ struct Layout {
   size_t rtab = 0, wtab = 0, rtab64 = 0, wtab64 = 0, paths = 0;
   size_t part_pa = 0, part_cc = 0, part_d = 0, bar = 0, prog = 0, slots = 0, stab = 0, aitems = 0, st = 0, abort = 0;
   size_t c = 0, p0 = 0, p1 = 0, t = 0, a = 0, u = 0, dtab = 0;
+  size_t uploaded = 0;   // the regions below it are written by the host at bind
   size_t total = 0;
 };
 
@@ -46,8 +47,7 @@ otfs_status fail(otfs_status st, const char* fmt, ...);
 otfs_status hip_fail(hipError_t e, const char* what);
 otfs_status validate_opts(const otfs_cg_opts* o, otfs_cg_opts* out);
 otfs_status validate_frame(const otfs_frame_desc& f, int idx, HostFrame* out);
-void delay_ramp(const HostFrame& f, int p, std::vector<double2>& out);
-void wrap_factors(const HostFrame& f, std::vector<double2>& out);
+void frame_tables(const HostFrame& f, float2* r32, float2* w32, double2* r64, double2* w64);
 void frame_scalars(const HostFrame& fr, const otfs_cg_opts& o, int tiles, const FrameDev& geo,
                    FrameDev* d);
 int default_tile_elems(int64_t total_elems, int cus);
@@ -178,9 +178,6 @@ struct otfs_plan {
   unsigned* d_qhead = nullptr;
   unsigned* d_abort = nullptr;
   // host copies of the uploaded tables (kept alive across the asynchronous copies)
-  std::vector<float2> h_rtab, h_wtab;
-  std::vector<double2> h_rtab64, h_wtab64;
-  std::vector<int2> h_paths;
   std::vector<otfs::FrameDev> h_frames;
   // kernel timing
   hipEvent_t ev_begin = nullptr, ev_end = nullptr;

@@ -334,19 +334,11 @@ void build_tables(bool refresh, Request* r) {
   const HostFrame& f = r->hf;
   const SlotLayout& L = r->L;
   char* in = static_cast<char*>(r->in.p);
-  std::vector<double2> r64, w64;
-  for (int p = 0; p < f.P; ++p) delay_ramp(f, p, r64);
-  wrap_factors(f, w64);
+  frame_tables(f, reinterpret_cast<float2*>(in + L.rtab), reinterpret_cast<float2*>(in + L.wtab),
+               refresh ? reinterpret_cast<double2*>(in + L.rtab64) : nullptr,
+               refresh ? reinterpret_cast<double2*>(in + L.wtab64) : nullptr);
   int2* paths = reinterpret_cast<int2*>(in + L.paths);
   for (int p = 0; p < f.P; ++p) paths[p] = make_int2(f.tau[p], f.nu[p]);
-  float2* r32 = reinterpret_cast<float2*>(in + L.rtab);
-  float2* w32 = reinterpret_cast<float2*>(in + L.wtab);
-  for (size_t i = 0; i < r64.size(); ++i) r32[i] = make_float2((float)r64[i].x, (float)r64[i].y);
-  for (size_t i = 0; i < w64.size(); ++i) w32[i] = make_float2((float)w64[i].x, (float)w64[i].y);
-  if (refresh) {
-    std::memcpy(in + L.rtab64, r64.data(), r64.size() * sizeof(double2));
-    std::memcpy(in + L.wtab64, w64.data(), w64.size() * sizeof(double2));
-  }
   FrameState st0{};
   st0.status = OTFS_FRAME_RUNNING;
   std::memcpy(in + L.st, &st0, sizeof st0);

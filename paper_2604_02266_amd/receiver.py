@@ -50,8 +50,8 @@ def receive(ypilot_td, ydata_td, M: int, N: int, lam: float, qam: int, theta: fl
     yp_dd = dzt(ypilot_td, M, N, stream=stream)
     y_dd = dzt(ydata_td, M, N, stream=stream)
     pilots = yp_dd.view(npk, 1, E).expand(npk, per, E).reshape(-1).contiguous()
-    plan = Plan([_Placeholder(M, N, capacity, lam, qam) for _ in range(nd)], max_iters=max_iters,
-                rel_tol=rel_tol, refresh_every=refresh_every, tune=False)
+    plan = Plan([_Placeholder(M, N, capacity, lam, qam)] * nd, max_iters=max_iters, rel_tol=rel_tol,
+                refresh_every=refresh_every, tune=False)
     npaths = plan.paths_from_pilot(pilots, theta, stream=stream)
     sym = torch.empty(nd * E, dtype=torch.uint8, device="cuda")
     stats = plan.new_stats()
