@@ -182,7 +182,8 @@ struct Window {   // of one direction (H or H^H)
 // every row, so the copy loops have no vector arithmetic (walking the window as one run of
 // 128-element pieces took 25 vector instructions per load).
 __device__ __forceinline__ void window_dma(__amdgpu_buffer_rsrc_t r, const Window& w, int WR, int WC,
-                                           int TR, int TC, int M, int N, lptr<u64> win) {
+                                           int TR, int TC, int M, int N, lptr<u64> win,
+                                           bool factors = true) {
   const int tid = tid_here();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
@@ -206,7 +207,7 @@ __device__ __forceinline__ void window_dma(__amdgpu_buffer_rsrc_t r, const Windo
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   const int nlo = max(0, -w.col0), nhi = max(0, w.col0 + w.cend - M), nw = nlo + nhi;
-  if (nw == 0) return;
+  if (nw == 0 || !factors) return;
   for (int q = lane; q < nw; q += 64) {
     const lptr<u64> col = win + (q < nlo ? q : w.cend - nw + q);
     const float sg = q < nlo ? -1.f : 1.f;
@@ -223,7 +224,7 @@ __device__ __forceinline__ void window_dma(__amdgpu_buffer_rsrc_t r, const Windo
 // The same window through registers, one element per lane: any M, any source view.
 template <class Src>
 __device__ __forceinline__ void window_fill(const Src& src, const Window& w, int WR, int WC, int M,
-                                            int N, lptr<u64> win) {
+                                            int N, lptr<u64> win, bool factors = true) {
   constexpr int U = 4;
   const int total = WR * WC;
   const int dr = kBlock / WC, dc = kBlock - dr * WC;
@@ -249,7 +250,7 @@ __device__ __forceinline__ void window_fill(const Src& src, const Window& w, int
     for (int u = 0; u < U; ++u) {
       if (e + u * kBlock < total) {
         float2 v = src.value(raw[u]);
-        if (col[u] < 0 || col[u] >= M) {
+        if (factors && (col[u] < 0 || col[u] >= M)) {
           const float2 f = w.wrow[row[u]];
           v = cmulf(v, make_float2(f.x, col[u] < 0 ? -f.y : f.y));
         }
@@ -545,7 +546,7 @@ __device__ __forceinline__ void cg_tile_item(const FrameDev& F, int tile, int bu
     if (!meet<true, false>(m, kMeetNorm, ++ep_norm, true, 0.f, &zero)) end = kTimeout;
     if (end == kRun && s.refresh) {   // after the refresh launches: the true residual's norm
       s.refresh = 0;
-      next(uniform_f((float)tile_sum_d(F.part_d, F.T)), false);
+      next(uniform_f((float)tile_sum_d(F.part_d, F.ref_T)), false);
     }
   }
   // One straight-line body for the start (b = H^H y) and every iteration, left at its end
@@ -825,6 +826,218 @@ hipError_t launch_apply_tile(bool adjoint, const FrameDev* frames, const int2* i
     hipLaunchKernelGGL(k_apply_tile<false>, dim3(nitems), dim3(kBlock), lds_bytes, s, frames, items,
                        nxcd, in, out);
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------
+// The FP64 refresh on the tiles of the solve, for batches that run whole on register-resident
+// tiles: u = y - H x (k_refresh_tile<false>), then c = H^H u - lam x and its
+// FP64 partial norms (<true>); x, u and c in FP32, products and sums in FP64.
+//
+// Windows as in the applications, but without the wrap factors, which would round in FP32.  The
+// factor of a wrapped gather depends on the output row alone, but for W[nu] of its path (H:
+// W[l0]^n with l0 = l - nu; H^H: conj(D) carries W[l]^n itself), so a tile at the frame's edge
+// runs its wrapped gathers first, times the row's factor once, and the others last; a lane's
+// coefficient is zero in the passes that its column has no part in.
+//
+// One workgroup per CU: a tile's window copy, path loop and stores follow one another.  128
+// frames of 1024 x 256 with 16 paths: 377 and 413 us against 627 and 567 us of the streaming
+// launches, whose windows of whole rows hold three times their band (of 392: 276 without the
+// path loop, 386 without the window copy; the vectors' 24 bytes per element alone take 146).
+// On the applications' cut, two workgroups per CU, windows 4.5 times the tile: 434 and 466;
+// elements read one path ahead: 411 and 447.
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ double2 ld_d2(__amdgpu_buffer_rsrc_t r, uint32_t vb, uint32_t sb) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, vb, sb, 0));
+}
+template <bool ADJ, int NJ, int CW, bool WRAPPED>
+__device__ __forceinline__ void refresh_paths(const Lanes<NJ, CW>& t, const TileBox& b, const FrameDev& F,
+                                              int off, int wrap, double2* acc) {
+  const __amdgpu_buffer_rsrc_t tab = buf_rsrc(F.rtab64, (int64_t)F.P * F.M * 16);
+  const int M = F.M, P = F.P;
+  auto column = [&](int w) __attribute__((always_inline)) { return (int)(t.k8[w] >> 3); };
+  // the coefficient of path p at the lane's column (ADJ: of the column it gathers from)
+  auto coef = [&](int p, double2* c) __attribute__((always_inline)) {
+    const int tau = ((kptr<const int>)F.paths)[2 * p];
+#pragma unroll
+    for (int w = 0; w < CW; ++w) {
+      const int k = ADJ ? wrap_once(column(w) + tau, M) : column(w);
+      c[w] = ld_d2(tab, 16u * (uint32_t)k, 16u * (uint32_t)(p * M));
+    }
+  };
+  auto rd = [&](int p, float2* v) __attribute__((always_inline)) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane(off, p);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const lptr<const u64> a = (lptr<const u64>)(uintptr_t)(t.la + o + (uint32_t)min(j, t.last) * t.lstep);
+      v[j * CW] = __builtin_bit_cast(float2, a[0]);
+      if (CW == 2) v[j * CW + 1] = __builtin_bit_cast(float2, a[64]);
+    }
+  };
+  auto mac = [&](int p, double2* c, const float2* v) __attribute__((always_inline)) {
+    const int tau = ((kptr<const int>)F.paths)[2 * p];
+#pragma unroll
+    for (int w = 0; w < CW; ++w) {
+      const int k = ADJ ? column(w) + tau : column(w) - tau;
+      if (wrap < 0 ? k >= 0 : (wrap > 0 ? k < M : (k < 0 || k >= M))) c[w] = make_double2(0.0, 0.0);
+      if (ADJ) c[w].y = -c[w].y;
+    }
+#pragma unroll
+    for (int i = 0; i < NJ * CW; ++i)
+      cmacd(acc[i], c[i % CW], make_double2((double)v[i].x, (double)v[i].y));
+  };
+  if constexpr (WRAPPED) {
+#pragma unroll 1
+    for (int p = 0; p < P; ++p) {
+      const int tau = ((kptr<const int>)F.paths)[2 * p], nu = ((kptr<const int>)F.paths)[2 * p + 1];
+      const int s0 = ADJ ? b.c0 + tau : b.c0 - tau, s1 = s0 + b.TC - 1;   // columns gathered from
+      if (wrap < 0 ? s0 >= 0 : s1 < M) continue;
+      double2 c[CW];
+      float2 v[NJ * CW];
+      coef(p, c);
+      rd(p, v);
+      if (!ADJ) {
+        double2 f = __builtin_bit_cast(double2, ((kptr<const u32x4>)F.wtab64)[nu < 0 ? nu + F.N : nu]);
+        if (wrap > 0) f.y = -f.y;
+#pragma unroll
+        for (int w = 0; w < CW; ++w) c[w] = cmuld(c[w], f);
+      }
+      mac(p, c, v);
+    }
+  } else {
+    double2 cn[CW];
+    coef(0, cn);
+#pragma unroll 1
+    for (int p = 0; p < P; ++p) {
+      double2 c[CW];
+      float2 v[NJ * CW];
+#pragma unroll
+      for (int w = 0; w < CW; ++w) c[w] = cn[w];
+      coef(min(p + 1, P - 1), cn);
+      rd(p, v);
+      mac(p, c, v);
+    }
+  }
+}
+template <bool ADJ, int NE, int CW>
+__device__ __forceinline__ void refresh_tile(const FrameDev& F, const FrameVecs& V, int tile, float2* lds,
+                                             double* red) {
+  constexpr int NJ = NE / CW;
+  const TileBox box = tile_box<CW>(F, F.tk_nbr, F.tk_nbc, F.tk_tc, tile);
+  const int64_t E = (int64_t)F.M * F.N;
+  const lptr<u64> win = (lptr<u64>)lds;
+  Window w = tile_window<ADJ>(F, box, nullptr);
+  const int off = path_offset<ADJ>(F, box, w, (int)threadIdx.x & 63);
+  const Lanes<NJ, CW> ln = tile_lanes<NJ, CW>(box, F.M, win);
+  const float2* in = ADJ ? F.u : V.x;
+  const __amdgpu_buffer_rsrc_t rin = buf_rsrc(in, E * 8);
+  if ((F.M & 1) == 0 && ((uintptr_t)in & 15u) == 0) {
+    w.orow = box.WR;
+    window_dma(rin, w, box.WR, box.WC, 0, 0, F.M, F.N, win, false);
+  } else {
+    window_fill(SrcBuf{rin}, w, box.WR, box.WC, F.M, F.N, win, false);
+  }
+  // y or x of the tile, on its way during the path loop (together with the window: +40 us)
+  float2 own[NE];
+#pragma unroll
+  for (int i = 0; i < NE; ++i) own[i] = make_float2(0.f, 0.f);
+  if (!ADJ && V.ybf16) {
+    tile_each(ln, [&](int i, int j, int c) __attribute__((always_inline)) {
+      own[i] = load_y(V.y, (ln.ov[c] + (uint32_t)j * ln.rstep) >> 3, true);
+    });
+  } else {
+    const __amdgpu_buffer_rsrc_t r = buf_rsrc(ADJ ? V.x : V.y, E * 8);
+    tile_each(ln, [&](int i, int j, int c) __attribute__((always_inline)) {
+      own[i] = buf_ld2b(r, ln.ov[c], (uint32_t)j * ln.rstep);
+    });
+  }
+  double2 acc[NE];
+#pragma unroll
+  for (int i = 0; i < NE; ++i) acc[i] = make_double2(0.0, 0.0);
+  // wrapped gathers: the sums W[l] hi + conj(W[l]) lo as (hi W[l]^2 + lo) conj(W[l])
+  const int c1 = box.c0 + box.TC - 1;
+  const bool lo = ADJ ? box.c0 + F.tau_lo < 0 : box.c0 - F.tau_hi < 0;
+  const bool hi = ADJ ? c1 + F.tau_hi >= F.M : c1 - F.tau_lo >= F.M;
+  if (lo || hi) {
+    auto rows = [&](bool square) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int l = min(box.r0 + box.ty + j * box.TY, F.N - 1);
+        double2 f = __builtin_bit_cast(double2, ((gptr<const u32x4>)F.wtab64)[l]);
+        f = square ? cmuld(f, f) : make_double2(f.x, -f.y);
+#pragma unroll
+        for (int c = 0; c < CW; ++c) acc[j * CW + c] = cmuld(acc[j * CW + c], f);
+      }
+    };
+    if (hi) {
+      refresh_paths<ADJ, NJ, CW, true>(ln, box, F, off, 1, acc);
+      rows(true);
+    }
+    if (lo) refresh_paths<ADJ, NJ, CW, true>(ln, box, F, off, -1, acc);
+    rows(false);
+  }
+  refresh_paths<ADJ, NJ, CW, false>(ln, box, F, off, 0, acc);
+  float2 res[NE];
+  if (ADJ) {
+    const double lam = (double)F.lam;
+#pragma unroll
+    for (int i = 0; i < NE; ++i)
+      res[i] = make_float2((float)(acc[i].x - lam * (double)own[i].x), (float)(acc[i].y - lam * (double)own[i].y));
+    tile_store(ln, buf_rsrc(F.c, E * 8), res);
+    double s = 0.0;
+    tile_each(ln, [&](int i, int, int) __attribute__((always_inline)) {
+      s = fma((double)res[i].x, (double)res[i].x, s);
+      s = fma((double)res[i].y, (double)res[i].y, s);
+    });
+    s = block_sum_d(s, red);
+    if (threadIdx.x == 0) F.part_d[tile] = s;
+  } else {
+#pragma unroll
+    for (int i = 0; i < NE; ++i)
+      res[i] = make_float2((float)((double)own[i].x - acc[i].x), (float)((double)own[i].y - acc[i].y));
+    tile_store(ln, buf_rsrc(F.u, E * 8), res);
+  }
+}
+// The launch boundaries order these kernels against the fused launches: no fence inside.
+template <bool ADJ, int NE>
+__global__ __launch_bounds__(kBlock, 2) void k_refresh_tile(const FrameDev* __restrict__ frames,
+                                                            const int2* __restrict__ items, int nxcd,
+                                                            Bases B, unsigned* qhead, int nq) {
+  __shared__ double red[kWaves];
+  extern __shared__ float2 tile_lds[];
+  const int2 it = items[xcd_item((int)gridDim.x, nxcd)];
+  const FrameDev& F = frames[it.x];
+  if (!ADJ) {   // for the next fused launch of the solve
+    if (blockIdx.x == 0 && (int)threadIdx.x < nq) qhead[threadIdx.x] = 0u;
+    if (it.y == 0 && (int)threadIdx.x < kTileMeets * F.tk_T) F.slots[threadIdx.x] = 0ull;
+  }
+  if (F.st->refresh == 0 || F.st->status != OTFS_FRAME_RUNNING) return;
+  const FrameVecs V = frame_vecs(F, B);
+  if (F.tk_cw == 2)
+    refresh_tile<ADJ, NE, 2>(F, V, it.y, tile_lds, red);
+  else
+    refresh_tile<ADJ, NE, 1>(F, V, it.y, tile_lds, red);
+}
+
+template <int NE>
+hipError_t refresh_tiles(const FrameDev* frames, const int2* items, int nitems, int nxcd, Bases bases,
+                         unsigned* qhead, int nq, int lds_bytes, hipStream_t s) {
+  const void* fns[] = {reinterpret_cast<const void*>(&k_refresh_tile<false, NE>),
+                       reinterpret_cast<const void*>(&k_refresh_tile<true, NE>)};
+  for (const void* fn : fns) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k_refresh_tile<false, NE>), dim3(nitems), dim3(kBlock), lds_bytes, s, frames, items,
+                     nxcd, bases, qhead, nq);
+  hipLaunchKernelGGL((k_refresh_tile<true, NE>), dim3(nitems), dim3(kBlock), lds_bytes, s, frames, items,
+                     nxcd, bases, qhead, nq);
+  return hipGetLastError();
+}
+hipError_t launch_refresh_tile(int kind, const FrameDev* frames, const int2* items, int nitems, int nxcd,
+                               Bases bases, unsigned* qhead, int nq, int lds_bytes, hipStream_t s) {
+  return kind == kKindTile
+             ? refresh_tiles<kTileElems>(frames, items, nitems, nxcd, bases, qhead, nq, lds_bytes, s)
+             : refresh_tiles<kTileElemsSmall>(frames, items, nitems, nxcd, bases, qhead, nq, lds_bytes, s);
 }
 
 hipError_t launch_tile_tables(const FrameDev* frames, int nframes, hipStream_t s) {

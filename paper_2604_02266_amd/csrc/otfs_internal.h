@@ -77,7 +77,7 @@ struct FrameDev {
   const void* dtab;       // stored D_{p,q}, P x E, bf16 pairs or complex64 (nullable)
   float* part_pa;         // T partial sums of Re(p^H a)
   float* part_cc;         // T partial sums of ||c||^2
-  double* part_d;         // T FP64 partial sums (refresh)
+  double* part_d;         // ref_T FP64 partial sums (refresh)
   unsigned* bar;          // arrival counter of the per-frame barrier
   unsigned* prog;         // T per-tile counters: phases whose rows the neighbours may gather
   FrameState* st;
@@ -115,6 +115,7 @@ struct FrameDev {
   unsigned long long* slots;
   // the cut of the standalone applications (ap_T = 0: by the streaming items)
   int32_t ap_T, ap_nbr, ap_nbc, ap_tc, ap_cw;
+  int32_t ref_T;          // FP64 partial sums that the refresh before a tile launch leaves
   float2* stab;           // P x M: the H^H coefficients by output column (k_tile_tables)
   // path capacity: the P given at otfs_plan; a path table estimated on the device from a
   // pilot frame (otfs_plan_paths_from_pilot) may set P to anything in [0, pcap]
@@ -232,6 +233,11 @@ int fused_blocks_per_cu(int kind, int sd, int lds_bytes);
 // the blocks of one XCD then take consecutive items, so a frame's tiles share its L2.
 hipError_t launch_refresh(const FrameDev* frames, const WorkItem* items, int nitems, Bases bases,
                           unsigned* qhead, int nq, int lds_bytes, int nxcd, hipStream_t s);
+// The same two launches on the frames' own tiles (nitems workgroups, items {frame, tile}), for
+// batches whose every frame is register-resident, all in one launch of kind `kind`.
+hipError_t launch_refresh_tile(int kind, const FrameDev* frames, const int2* items, int nitems, int nxcd,
+                               Bases bases, unsigned* qhead, int nq, int lds_bytes, hipStream_t s);
+
 
 // Static scratch of the entry point that allocates nothing: kNoAllocBytes per device.
 // *ptr = its device address on `device`, which must be the current device (found once per

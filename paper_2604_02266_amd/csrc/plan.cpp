@@ -703,12 +703,15 @@ void compute_layout(otfs_plan_t* pl) {
   L.wtab64 = refresh ? take(wt * sizeof(double2)) : 0;
   L.paths = take(np * sizeof(int2));
   L.aitems = pl->apply_items.empty() ? 0 : take(pl->apply_items.size() * sizeof(int2));
+  L.ritems = refresh && ntiles ? take(ntiles * sizeof(int2)) : 0;
   L.uploaded = o;
   L.qhead = take(kKinds * kMaxGroups * sizeof(unsigned));
   L.probe = take(kProbeBlocks * sizeof(int));
   L.part_pa = take(nitems * sizeof(float));
   L.part_cc = take(nitems * sizeof(float));
-  L.part_d = take(nitems * sizeof(double));
+  size_t npart = 0;
+  for (size_t f = 0; f < nf; ++f) npart += (size_t)std::max(pl->tiles[f], pl->cuts[f].T);
+  L.part_d = take(npart * sizeof(double));
   L.bar = take(nf * sizeof(unsigned));
   L.prog = take(nitems * sizeof(unsigned));
   L.stab = sb ? take(sb * sizeof(float2)) : 0;
@@ -1007,12 +1010,21 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
   // host tables
   const Layout& L = plan->L;
   char* base = static_cast<char*>(ws);
+  // The refresh runs on the solve's tiles when every frame is register-resident (and the paths
+  // are the host's); a batch with other frames keeps the work items of the streaming kinds,
+  // whose sums are those frames' too.
+  plan->ref_tiles = tiles_on && plan->launches.size() == 1;
+  std::vector<int2> ref_items;
+  for (size_t f = 0; f < plan->frames.size(); ++f) {
+    plan->ref_tiles = plan->ref_tiles && geo[f].tk_T > 0;
+    for (int t = 0; t < geo[f].tk_T; ++t) ref_items.push_back(make_int2((int)f, t));
+  }
   // the uploaded regions as they lie in the workspace: one copy
   std::unique_ptr<char[]> host(new (std::nothrow) char[L.uploaded]);
   if (!host) return fail(OTFS_E_NOMEM, "out of host memory");
   auto at = [&](size_t off) { return host.get() + off; };
   std::vector<FrameDev> fd(plan->frames.size());
-  size_t ro = 0, wo = 0, po = 0, dto = 0, so = 0, sbo = 0;
+  size_t ro = 0, wo = 0, po = 0, dto = 0, so = 0, sbo = 0, pdo = 0;
   const bool refresh = plan->opts.refresh_every > 0;
   const int sd = stored_mode(plan->opts.flags);
   const size_t dsz = sd == kDC64 ? sizeof(float2) : sizeof(uint32_t);
@@ -1042,7 +1054,9 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
     const int tb = plan->tile_base[f];
     d.part_pa = reinterpret_cast<float*>(base + L.part_pa) + tb;
     d.part_cc = reinterpret_cast<float*>(base + L.part_cc) + tb;
-    d.part_d = reinterpret_cast<double*>(base + L.part_d) + tb;
+    d.part_d = reinterpret_cast<double*>(base + L.part_d) + pdo;
+    pdo += (size_t)std::max(plan->tiles[f], plan->cuts[f].T);
+    d.ref_T = plan->ref_tiles ? plan->cuts[f].T : plan->tiles[f];
     d.bar = reinterpret_cast<unsigned*>(base + L.bar) + f;
     d.prog = reinterpret_cast<unsigned*>(base + L.prog) + tb;
     d.slots = reinterpret_cast<unsigned long long*>(base + L.slots) + so;
@@ -1071,6 +1085,8 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
   put(L.qitems, plan->qitems.data(), plan->qitems.size() * sizeof(int32_t));
   put(L.qrange, plan->qrange.data(), plan->qrange.size() * sizeof(int2));
   put(L.aitems, plan->apply_items.data(), plan->apply_items.size() * sizeof(int2));
+  if (refresh) put(L.ritems, ref_items.data(), ref_items.size() * sizeof(int2));
+  plan->nritems = (int)ref_items.size();
   plan->h_frames = std::move(fd);
   if (L.uploaded > 0 &&
       (e = hipMemcpyAsync(base, host.get(), L.uploaded, hipMemcpyHostToDevice, s)) != hipSuccess)
@@ -1087,6 +1103,7 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
       return hip_fail(e, "build D");
   }
   plan->d_aitems = reinterpret_cast<int2*>(base + L.aitems);
+  plan->d_ritems = reinterpret_cast<int2*>(base + L.ritems);
   if ((tiles_on || !plan->apply_items.empty()) && (e = launch_tile_tables(plan->d_frames, (int)plan->frames.size(), s)) != hipSuccess)
     return hip_fail(e, "tile tables");
   // the host copy must outlive the transfer
@@ -1180,7 +1197,11 @@ static hipError_t enqueue_fused(otfs_plan_t* plan, const Bases& B, hipStream_t s
                           plan->d_abort, L.lds_bytes, plan->wait_us, s);
       if (e != hipSuccess) return e;
     }
-    if (seg + 1 < nseg) {
+    if (seg + 1 < nseg && plan->ref_tiles && !plan->device_paths) {
+      e = launch_refresh_tile(launches[0].kind, plan->d_frames, plan->d_ritems, plan->nritems, plan->ref_xcds,
+                              B, plan->d_qhead, kKinds * kMaxGroups, launches[0].lds_bytes, s);
+      if (e != hipSuccess) return e;
+    } else if (seg + 1 < nseg) {
       e = launch_refresh(plan->d_frames, plan->d_items, (int)plan->items.size(), B,
                          plan->d_qhead, kKinds * kMaxGroups, refresh_lds_bytes(launches),
                          plan->ref_xcds, s);

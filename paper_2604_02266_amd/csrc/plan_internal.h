@@ -26,7 +26,7 @@ struct HostFrame {
 struct Layout {
   size_t frames = 0, items = 0, qitems = 0, qrange = 0, qhead = 0, probe = 0;
   size_t rtab = 0, wtab = 0, rtab64 = 0, wtab64 = 0, paths = 0;
-  size_t part_pa = 0, part_cc = 0, part_d = 0, bar = 0, prog = 0, slots = 0, stab = 0, aitems = 0, st = 0, abort = 0;
+  size_t part_pa = 0, part_cc = 0, part_d = 0, bar = 0, prog = 0, slots = 0, stab = 0, aitems = 0, ritems = 0, st = 0, abort = 0;
   size_t c = 0, p0 = 0, p1 = 0, t = 0, a = 0, u = 0, dtab = 0;
   size_t uploaded = 0;   // the regions below it are written by the host at bind
   size_t total = 0;
@@ -151,6 +151,9 @@ struct otfs_plan {
   std::vector<int2> apply_items;       // {frame, tile} of the apply cuts
   int apply_lds = 0;                   // largest window of the apply cuts, bytes
   bool apply_all = false;              // every frame has an apply cut
+  bool ref_tiles = false;              // the FP64 refresh runs on the tiles of the solve
+  int nritems = 0;                     // ... one item per tile
+  int2* d_ritems = nullptr;
   int win_w_req = 0, win_rc_req = 0;   // windowed form (0: off)
   std::vector<int> winw;               // per frame: strip width of the windowed form, or 0
   // tiling (host) and schedule (chosen at bind)
