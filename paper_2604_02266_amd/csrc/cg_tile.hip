@@ -720,9 +720,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_cg_tile(const FrameDev* __restric
   __shared__ float s_out;
   __shared__ int s_ok, s_item;
   extern __shared__ float2 tile_lds[];
-  // data this launch reads may have been written on other XCDs: one device-wide acquire
-  // before the first read, one release at the end
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  // (the launch boundaries order this launch's data against other XCDs' writes)
   const int g = xcc_id();
   if (g < ngroups) {
     const int2 r = qrange[g];
@@ -754,7 +752,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_cg_tile(const FrameDev* __restric
       __syncthreads();
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
 }
 
 }  // namespace
