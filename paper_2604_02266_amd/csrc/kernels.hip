@@ -458,10 +458,13 @@ constexpr int kElemChunkLds = OTFS_ELEM_CHUNK_LDS;   // and in the windowed-pair
 #define OTFS_RES_ROWS 2
 #endif
 #ifndef OTFS_RES_PATHS
-#define OTFS_RES_PATHS 1
+#define OTFS_RES_PATHS 2
 #endif
 constexpr int kResRows = OTFS_RES_ROWS;    // rows per chunk of the LDS-resident gathers
-constexpr int kResPaths = OTFS_RES_PATHS;  // paths per step of the LDS-resident gathers
+// paths per step of the LDS-resident gathers: the table reads and LDS reads of two paths are in
+// flight together (one frame of 64 x 16, 30 iterations: one 144 us, two 133, four 136; 1024
+// such frames: 362, 331, 337)
+constexpr int kResPaths = OTFS_RES_PATHS;
 
 template <int R, int U, bool ADJ, int SD, bool UNI, class A, class Src, class Pref, class Sink>
 __device__ __forceinline__ void band_apply_rows(const FrameDev& F, int lb, int le, const Src& src,
