@@ -218,10 +218,14 @@ class _Descs:
             tau = np.ascontiguousarray(f.tau, dtype=np.int32)
             nu = np.ascontiguousarray(f.nu, dtype=np.int32)
             self.keep += [h, tau, nu]
-            rows.append((int(f.M), int(f.N), tau.shape[0], _address(h), _address(tau), _address(nu),
-                         float(f.lam), int(getattr(f, "qam", 0) or 0)))
+            rows.append((_int32(f.M), _int32(f.N), tau.shape[0], _address(h), _address(tau), _address(nu),
+                         ctypes.c_float(float(f.lam)).value, _int32(getattr(f, "qam", 0) or 0)))
         self.arr = (FrameDesc * max(len(frames), 1)).from_buffer(
             np.array(rows, dtype=_DESC) if rows else np.zeros(1, dtype=_DESC))
+
+
+def _int32(v) -> int:
+    return ctypes.c_int32(int(v)).value   # (wraps as a ctypes field does; the library refuses it)
 
 
 def _address(a) -> int:

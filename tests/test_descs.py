@@ -48,3 +48,10 @@ def test_records_of_no_frames_and_gains_copied():
     d = otfs._Descs([Spec(h, [0, 1, 2], [0, 0, 0])])
     h[0] = 9
     assert d.arr[0].h[0] == 0.5
+
+
+def test_values_beyond_the_fields_as_ctypes_stores_them():
+    f = Spec(G, [0, 1, 2], [0, 0, 0], qam=2 ** 33 + 4)
+    f.M, f.N, f.lam = 2 ** 31, np.int64(2 ** 32 + 8), 1e39
+    d = otfs._Descs([f]).arr[0]
+    assert (d.M, d.N, d.qam, d.noise_var) == (-2 ** 31, 8, 4, float("inf"))
