@@ -2247,14 +2247,19 @@ __device__ void cg_item_resident(const FrameDev& F, int budget, const Bases& B, 
 #ifndef OTFS_LDS_MIN_WAVES
 #define OTFS_LDS_MIN_WAVES 4
 #endif
-constexpr int fused_min_waves(int kind) {
-  return kind == kKindWindowed ? OTFS_WIN_MIN_WAVES
+// The bf16 coefficient table's reads are a quarter of the paired gathers', and two workgroups per
+// CU (128 VGPRs, 2 spilled) run the rounds of a batch together: 16 frames of 512 x 128 1058 ->
+// 927 us, 64 of them 2350 -> 2174, 128 of 256 x 64 1305 -> 1122; batches of one round lose up
+// to 1 % (20 of 300 x 70: 547 -> 553).  The complex64 table's do not gain (64 of 512 x 128: 2875
+// -> 3150), nor the synthesised coefficients (pilot batch: 776 -> 873).
+constexpr int fused_min_waves(int kind, int sd) {
+  return sd == kDBf16 ? 4 : kind == kKindWindowed ? OTFS_WIN_MIN_WAVES
                                : ((kind == kKindDirect || kind == kKindDirectFD || kind == kKindLds)
                                       ? OTFS_FUSED_MIN_WAVES
                                       : OTFS_LDS_MIN_WAVES);
 }
 template <int SD, int KIND>
-__global__ __launch_bounds__(kBlock, fused_min_waves(KIND)) void k_cg_fused(const FrameDev* __restrict__ frames,
+__global__ __launch_bounds__(kBlock, fused_min_waves(KIND, SD)) void k_cg_fused(const FrameDev* __restrict__ frames,
                                                      const WorkItem* __restrict__ items,
                                                      const int32_t* __restrict__ qitems,
                                                      const int2* __restrict__ qrange,
