@@ -2603,6 +2603,7 @@ __device__ __forceinline__ double2 unit_phasor(int64_t num, int64_t mn) {
   return make_double2(cs, sn);
 }
 
+constexpr int kPilotGroup = 8;
 __global__ __launch_bounds__(kBlock) void k_pilot_paths(FrameDev* __restrict__ frames,
                                                         const float2* __restrict__ ypilot,
                                                         float theta, int32_t* npaths) {
@@ -2617,38 +2618,65 @@ __global__ __launch_bounds__(kBlock) void k_pilot_paths(FrameDev* __restrict__ f
   const float th2 = __fmul_rn(theta, theta);
   const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
   int base = 0;
-  for (int64_t q0 = 0; q0 < E; q0 += kBlock) {
-    const int64_t q = q0 + threadIdx.x;
-    bool sel = false;
-    float2 h = make_float2(0.f, 0.f);
-    int k = 0, l = 0;
-    if (q < E) {
-      l = (int)(q / M);
-      k = (int)(q - (int64_t)l * M);
-      const double2 tw = unit_phasor(-(int64_t)K0 * (l - L0), MN);
-      const float2 y = yp.f(q);
-      h = make_float2((float)((double)y.x * tw.x - (double)y.y * tw.y),
-                      (float)((double)y.x * tw.y + (double)y.y * tw.x));
-      sel = __fadd_rn(__fmul_rn(h.x, h.x), __fmul_rn(h.y, h.y)) > th2;
+  // kPilotGroup runs of 512 bins are read at once, and a run is passed over when none of its bins
+  // can exceed theta: the rotation keeps |y| to a few FP32 roundings (below 1e-6), so a bin with
+  // |y|^2 < (1 - 1e-4) theta^2 is not selected (a theta^2 near the underflow tests every bin).
+  // The runs' FP64 rotations and two meetings each had taken 152 us for 512 x 128 bins, one
+  // workgroup per frame; with most runs passed over it is 40 us.
+  const float near = th2 > 1e-30f ? th2 * 0.9999f : 0.f;
+  for (int64_t q0 = 0; q0 < E; q0 += kPilotGroup * kBlock) {
+    float2 v[kPilotGroup];
+#pragma unroll
+    for (int g = 0; g < kPilotGroup; ++g) {
+      const int64_t q = q0 + g * kBlock + threadIdx.x;
+      v[g] = q < E ? yp.f(q) : make_float2(0.f, 0.f);
     }
-    const uint64_t m = __builtin_amdgcn_ballot_w64(sel);
-    const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    if (lane == 0) wcount[wave] = __popcll(m);
+    int some = 0;   // bit g: a bin of run g of this wave may be selected
+#pragma unroll
+    for (int g = 0; g < kPilotGroup; ++g) {
+      const bool below = fmaf(v[g].x, v[g].x, v[g].y * v[g].y) < near;   // (false for NaN)
+      const bool may = !below && q0 + g * kBlock + threadIdx.x < E;
+      some |= __builtin_amdgcn_ballot_w64(may) != 0 ? 1 << g : 0;
+    }
+    if (lane == 0) wcount[wave] = some;
     __syncthreads();
-    int woff = 0, total = 0;
-    for (int w = 0; w < kWaves; ++w) {
-      const int c = wcount[w];
-      woff += w < wave ? c : 0;
-      total += c;
-    }
-    const int idx = base + woff + before;
-    if (sel && idx < cap) {
-      s_tn[idx] = make_int2(k - K0, l - L0);
-      s_gain[idx] = h;
-    }
-    base += total;
+    for (int w = 0; w < kWaves; ++w) some |= wcount[w];
     __syncthreads();
+#pragma unroll 1
+    for (int g = 0; g < kPilotGroup; ++g) {
+      if (!(some >> g & 1)) continue;
+      const int64_t q = q0 + g * kBlock + threadIdx.x;
+      bool sel = false;
+      float2 h = make_float2(0.f, 0.f);
+      int k = 0, l = 0;
+      if (q < E) {
+        l = (int)(q / M);
+        k = (int)(q - (int64_t)l * M);
+        const double2 tw = unit_phasor(-(int64_t)K0 * (l - L0), MN);
+        const float2 y = yp.f(q);
+        h = make_float2((float)((double)y.x * tw.x - (double)y.y * tw.y),
+                        (float)((double)y.x * tw.y + (double)y.y * tw.x));
+        sel = __fadd_rn(__fmul_rn(h.x, h.x), __fmul_rn(h.y, h.y)) > th2;
+      }
+      const uint64_t m = __builtin_amdgcn_ballot_w64(sel);
+      const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      if (lane == 0) wcount[wave] = __popcll(m);
+      __syncthreads();
+      int woff = 0, total = 0;
+      for (int w = 0; w < kWaves; ++w) {
+        const int c = wcount[w];
+        woff += w < wave ? c : 0;
+        total += c;
+      }
+      const int idx = base + woff + before;
+      if (sel && idx < cap) {
+        s_tn[idx] = make_int2(k - K0, l - L0);
+        s_gain[idx] = h;
+      }
+      base += total;
+      __syncthreads();
+    }
   }
   const int P = base < cap ? base : cap;
   int2* const paths = const_cast<int2*>(F.paths);
