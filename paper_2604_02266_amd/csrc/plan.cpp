@@ -1175,6 +1175,18 @@ static int fused_segments(const otfs_cg_opts& o) {
   return o.refresh_every > 0 ? (o.max_iters - 1) / o.refresh_every + 1 : 1;
 }
 
+// The two launches of the FP64 refresh, on the tiles that the next fused launch sums the
+// partial norms of (FrameDev::ref_T).
+static hipError_t enqueue_refresh(otfs_plan_t* plan, const Bases& B, hipStream_t s) {
+  const std::vector<KindLaunch>& launches = plan->solve_launches();
+  if (plan->ref_tiles && !plan->device_paths)
+    return launch_refresh_tile(launches[0].kind, plan->d_frames, plan->d_ritems, plan->nritems,
+                               plan->ref_xcds, B, plan->d_qhead, kKinds * kMaxGroups,
+                               launches[0].lds_bytes, s);
+  return launch_refresh(plan->d_frames, plan->d_items, (int)plan->items.size(), B, plan->d_qhead,
+                        kKinds * kMaxGroups, refresh_lds_bytes(launches), plan->ref_xcds, s);
+}
+
 // the launch sequence of one fused solve: reset, then per segment the persistent kernel of
 // every launch kind followed by the refresh launches (optionally timed as a whole)
 static hipError_t enqueue_fused(otfs_plan_t* plan, const Bases& B, hipStream_t s, bool timed) {
@@ -1197,16 +1209,7 @@ static hipError_t enqueue_fused(otfs_plan_t* plan, const Bases& B, hipStream_t s
                           plan->d_abort, L.lds_bytes, plan->wait_us, s);
       if (e != hipSuccess) return e;
     }
-    if (seg + 1 < nseg && plan->ref_tiles && !plan->device_paths) {
-      e = launch_refresh_tile(launches[0].kind, plan->d_frames, plan->d_ritems, plan->nritems, plan->ref_xcds,
-                              B, plan->d_qhead, kKinds * kMaxGroups, launches[0].lds_bytes, s);
-      if (e != hipSuccess) return e;
-    } else if (seg + 1 < nseg) {
-      e = launch_refresh(plan->d_frames, plan->d_items, (int)plan->items.size(), B,
-                         plan->d_qhead, kKinds * kMaxGroups, refresh_lds_bytes(launches),
-                         plan->ref_xcds, s);
-      if (e != hipSuccess) return e;
-    }
+    if (seg + 1 < nseg && (e = enqueue_refresh(plan, B, s)) != hipSuccess) return e;
   }
   if (timed && (e = hipEventRecord(plan->ev_end, s)) != hipSuccess) return e;
   return hipSuccess;
@@ -1329,9 +1332,7 @@ extern "C" otfs_status otfs_lmmse_cg_trace(otfs_plan_t* plan, const void* y, voi
   for (int it = 0; it < plan->opts.max_iters && e == hipSuccess; ++it) {
     if (it > 0) {   // counters and cursors of the next one-iteration launch
       e = plan->opts.refresh_every > 0
-              ? launch_refresh(plan->d_frames, plan->d_items, ni, B, plan->d_qhead,
-                               kKinds * kMaxGroups, refresh_lds_bytes(plan->solve_launches()),
-                               plan->ref_xcds, s)
+              ? enqueue_refresh(plan, B, s)
               : launch_step_reset(plan->d_frames, nf, plan->d_abort, plan->d_qhead,
                                   kKinds * kMaxGroups, s);
     }
