@@ -546,7 +546,7 @@ __device__ __forceinline__ void cg_tile_item(const FrameDev& F, int tile, int bu
     if (!meet<true, false>(m, kMeetNorm, ++ep_norm, true, 0.f, &zero)) end = kTimeout;
     if (end == kRun && s.refresh) {   // after the refresh launches: the true residual's norm
       s.refresh = 0;
-      next(uniform_f((float)tile_sum_d(F.part_d, F.ref_T)), false);
+      next(uniform_f((float)tile_sum_d<false>(F.part_d, F.ref_T)), false);
     }
   }
   // One straight-line body for the start (b = H^H y) and every iteration, left at its end

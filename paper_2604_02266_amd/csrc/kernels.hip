@@ -1622,6 +1622,12 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
     nbar += (unsigned)T;
     return frame_barrier(F.bar, nbar, L.xcd_local != 0, L.abort_flag, L.timeout, sflag);
   };
+  // after bar(), whose device-wide form invalidates the L1 (the stored tables' kinds, whose
+  // registers are full, keep one form: 0.7 % slower with both)
+  auto sum_tiles = [&](const float* part) {
+    if (SD == kDNone && !L.xcd_local) return tile_sum<false>(part, T);
+    return tile_sum<true>(part, T);
+  };
   // tiles whose rows the H pass (rows l - nu) and the H^H pass (rows l + nu) read
   const int span = le - lb + (F.nu_hi - F.nu_lo);
   const TileRange rd_h = tiles_of_rows(lb - F.nu_hi, span, F.N, T);
@@ -1659,7 +1665,7 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
     const float bs = block_sum(acc, red);
     if (threadIdx.x == 0) F.part_cc[wi.tile] = bs;
     if (!bar()) return fail_timeout();
-    const float cn0 = tile_sum(F.part_cc, T);
+    const float cn0 = sum_tiles(F.part_cc);
     s.init = 1;
     s.iter = 0;
     s.pbuf = 0;
@@ -1698,7 +1704,7 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
   };
   if (s.refresh) {   // resume after the refresh launches: the true residual's norm
     s.refresh = 0;
-    if (!next((float)tile_sum_d(F.part_d, T), false, F.p0)) return;
+    if (!next((float)tile_sum_d<false>(F.part_d, T), false, F.p0)) return;
   }
 
   for (int step = 0; step < budget; ++step) {
@@ -1785,7 +1791,7 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
     s.pbuf ^= 1;
     s.pending = 0;                                   // both deferred updates are applied
 
-    const float den = tile_sum(F.part_pa, T);
+    const float den = sum_tiles(F.part_pa);
     const float alpha = s.cn / den;
     if (!(den > 0.f) || !isfinite(alpha)) {          // x already holds x_{xi-1}
       const int st = (isfinite(den) && isfinite(s.cn)) ? OTFS_FRAME_BREAKDOWN
@@ -1868,7 +1874,7 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
       if (threadIdx.x == 0) F.part_cc[wi.tile] = bs;
     }
     if (!bar()) return fail_timeout();
-    const float cn_new = tile_sum(F.part_cc, T);
+    const float cn_new = sum_tiles(F.part_cc);
     s.iter = xi;
     s.alpha = alpha;
     if (refresh_due) {
@@ -1885,7 +1891,7 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
           if (threadIdx.x == 0) F.part_d[wi.tile] = bs;
           if (!bar()) return fail_timeout();
           s.pending = 0;
-          if (!next((float)tile_sum_d(F.part_d, T), false, F.p0)) return;
+          if (!next((float)tile_sum_d<true>(F.part_d, T), false, F.p0)) return;
           continue;
         }
       }
@@ -1941,6 +1947,9 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     nbar += (unsigned)T;
     return frame_barrier(F.bar, nbar, L.xcd_local != 0, L.abort_flag, L.timeout, sflag);
   };
+  auto sum_tiles = [&](const float* part) {   // after bar(), whose device-wide form invalidates the L1
+    return L.xcd_local ? tile_sum<true>(part, T) : tile_sum<false>(part, T);
+  };
   // strips whose columns the H^H pass gathers: [k0 + tau_lo, k0 + W - 1 + tau_hi] (mod M)
   const TileRange rd_hh = tiles_of_rows(k0 + F.tau_lo, W + (F.tau_hi - F.tau_lo), M, T);
   unsigned npub = 0;
@@ -1983,7 +1992,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     const float bs = block_sum(acc, red);
     if (threadIdx.x == 0) F.part_cc[wi.tile] = bs;
     if (!bar()) return fail_timeout();
-    const float cn0 = tile_sum(F.part_cc, T);
+    const float cn0 = sum_tiles(F.part_cc);
     s.init = 1;
     s.iter = 0;
     s.pbuf = 0;
@@ -2041,7 +2050,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     if (!bar()) return fail_timeout();
     s.pbuf ^= 1;
     s.pending = 0;
-    const float den = tile_sum(F.part_pa, T);
+    const float den = sum_tiles(F.part_pa);
     const float alpha = s.cn / den;
     if (!(den > 0.f) || !isfinite(alpha)) {
       const int st = (isfinite(den) && isfinite(s.cn)) ? OTFS_FRAME_BREAKDOWN
@@ -2076,7 +2085,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
       if (threadIdx.x == 0) F.part_cc[wi.tile] = bs;
     }
     if (!bar()) return fail_timeout();
-    const float cn_new = tile_sum(F.part_cc, T);
+    const float cn_new = sum_tiles(F.part_cc);
     s.iter = xi;
     s.alpha = alpha;
     s.rel = sqrtf(cn_new / s.cn0);
@@ -2741,7 +2750,7 @@ __global__ __launch_bounds__(kBlock) void k_plain_init(const FrameDev* __restric
 __global__ void k_plain_start(const FrameDev* __restrict__ frames, int f) {
   if (threadIdx.x != 0) return;
   const FrameDev& F = frames[f];
-  const float cn0 = tile_sum(F.part_cc, F.T);
+  const float cn0 = tile_sum<false>(F.part_cc, F.T);
   FrameState s = *F.st;
   s.cn0 = cn0;
   s.cn_hist[0] = cn0;
@@ -2794,7 +2803,7 @@ __global__ __launch_bounds__(kBlock) void k_plain_update(const FrameDev* __restr
   const FrameVecs V = frame_vecs(F, B);
   const WorkItem wi = items[blockIdx.x];
   const float cn = st->cn_hist[(xi - 1) & 1];
-  const float den = tile_sum(F.part_pa, F.T);
+  const float den = tile_sum<false>(F.part_pa, F.T);
   const float alpha = cn / den;
   if (!(den > 0.f) || !isfinite(alpha)) {
     if (blockIdx.x == 0 && threadIdx.x == 0)
@@ -2822,7 +2831,7 @@ __global__ __launch_bounds__(kBlock) void k_plain_dir(const FrameDev* __restrict
   if (st->status != OTFS_FRAME_RUNNING) return;
   const WorkItem wi = items[blockIdx.x];
   const float cn = st->cn_hist[(xi - 1) & 1];
-  const float cn_new = tile_sum(F.part_cc, F.T);
+  const float cn_new = tile_sum<false>(F.part_cc, F.T);
   const float rel = sqrtf(cn_new / st->cn0);
   int status = OTFS_FRAME_RUNNING;
   if (!isfinite(cn_new))
