@@ -313,8 +313,10 @@ otfs_status otfs_plan_paths_from_pilot(otfs_plan_t* plan, const void* ypilot_dev
  * library's static scratch on the current device (a workspace of at most 64 MiB, one copy
  * per GPU, held until the process ends), then runs otfs_lmmse_cg: same kernels, same
  * results.  Calls no hipMalloc / hipFree.  The caller still passes y, x_hat, the
- * decisions and the stats.  A plan whose otfs_plan_workspace_bytes() exceeds 64 MiB
- * returns OTFS_E_NOMEM; OTFS_USE_GRAPH or OTFS_TIME_KERNEL return OTFS_E_UNSUPPORTED.
+ * decisions and the stats.  A plan whose otfs_plan_workspace_bytes() exceeds 64 MiB, but
+ * only with the register-resident tiles' tables, runs on the streaming kinds here (the
+ * sums in their order); one that exceeds it without them returns OTFS_E_NOMEM and stays
+ * bound as it was.  OTFS_USE_GRAPH or OTFS_TIME_KERNEL return OTFS_E_UNSUPPORTED.
  * Every call rebinds the plan (table uploads on `stream`, then a synchronisation of it).
  * All calls on one GPU share the scratch: calls that overlap in time on one GPU race, and
  * the plan stays bound to the scratch afterwards. */

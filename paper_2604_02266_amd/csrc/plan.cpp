@@ -1087,6 +1087,7 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
   put(L.aitems, plan->apply_items.data(), plan->apply_items.size() * sizeof(int2));
   if (refresh) put(L.ritems, ref_items.data(), ref_items.size() * sizeof(int2));
   plan->nritems = (int)ref_items.size();
+  plan->bound_apply = BoundApply{(int)plan->apply_items.size(), plan->apply_lds, plan->apply_all};
   plan->h_frames = std::move(fd);
   if (L.uploaded > 0 &&
       (e = hipMemcpyAsync(base, host.get(), L.uploaded, hipMemcpyHostToDevice, s)) != hipSuccess)
@@ -1147,13 +1148,14 @@ static otfs_status apply_common(const otfs_plan_t* plan, bool adj, const void* i
       lds = std::max(lds, win_lds_bytes(d.win_w, d.win_rc, d.tau_hi - d.tau_lo, d.nu_hi - d.nu_lo));
   // frames with an apply cut (planned for the host's path tables) in one launch, the others
   // by the streaming items
-  const bool cut = !plan->device_paths && !plan->apply_items.empty();
+  const BoundApply& ap = plan->bound_apply;
+  const bool cut = !plan->device_paths && ap.items > 0;
   hipError_t e = hipSuccess;
   if (cut)
-    e = launch_apply_tile(adj, plan->d_frames, plan->d_aitems, (int)plan->apply_items.size(),
-                          plan->ref_xcds, static_cast<const float2*>(in), static_cast<float2*>(out),
-                          plan->apply_lds, static_cast<hipStream_t>(stream));
-  if (e == hipSuccess && !(cut && plan->apply_all))
+    e = launch_apply_tile(adj, plan->d_frames, plan->d_aitems, ap.items, plan->ref_xcds,
+                          static_cast<const float2*>(in), static_cast<float2*>(out), ap.lds,
+                          static_cast<hipStream_t>(stream));
+  if (e == hipSuccess && !(cut && ap.all))
     e = launch_apply(adj, sd, plan->d_frames, plan->d_items, (int)plan->items.size(),
                      static_cast<const float2*>(in), static_cast<float2*>(out), lds, cut,
                      static_cast<hipStream_t>(stream));
@@ -1420,17 +1422,8 @@ extern "C" otfs_status otfs_plan_paths_from_pilot(otfs_plan_t* plan, const void*
   return OTFS_OK;
 }
 
-extern "C" otfs_status otfs_lmmse_cg_noalloc(otfs_plan_t* plan, const void* y, void* xhat,
-                                             uint8_t* sym, otfs_frame_stats* stats, void* stream) {
-  if (!plan) return fail(OTFS_E_INVAL, "plan is null");
-  if (plan->opts.flags & (OTFS_USE_GRAPH | OTFS_TIME_KERNEL))
-    return fail(OTFS_E_UNSUPPORTED,
-                "otfs_lmmse_cg_noalloc runs without OTFS_USE_GRAPH and OTFS_TIME_KERNEL");
-  if (plan->L.total > kNoAllocBytes) {   // the streaming kinds' workspace may still fit
-    plan->no_tiles = true;
-    retile(plan);
-    plan->bound = false;
-  }
+static otfs_status solve_on_scratch(otfs_plan_t* plan, const void* y, void* xhat, uint8_t* sym,
+                                    otfs_frame_stats* stats, void* stream) {
   if (plan->L.total > kNoAllocBytes)
     return fail(OTFS_E_NOMEM,
                 "the plan needs a workspace of %zu bytes; the static scratch holds %zu bytes",
@@ -1446,6 +1439,23 @@ extern "C" otfs_status otfs_lmmse_cg_noalloc(otfs_plan_t* plan, const void* y, v
   otfs_status st = otfs_plan_bind(plan, ws, kNoAllocBytes, stream);
   if (st != OTFS_OK) return st;
   return otfs_lmmse_cg(plan, y, xhat, sym, stats, stream);
+}
+
+extern "C" otfs_status otfs_lmmse_cg_noalloc(otfs_plan_t* plan, const void* y, void* xhat,
+                                             uint8_t* sym, otfs_frame_stats* stats, void* stream) {
+  if (!plan) return fail(OTFS_E_INVAL, "plan is null");
+  if (plan->opts.flags & (OTFS_USE_GRAPH | OTFS_TIME_KERNEL))
+    return fail(OTFS_E_UNSUPPORTED,
+                "otfs_lmmse_cg_noalloc runs without OTFS_USE_GRAPH and OTFS_TIME_KERNEL");
+  if (plan->L.total <= kNoAllocBytes) return solve_on_scratch(plan, y, xhat, sym, stats, stream);
+  // the streaming kinds' workspace may still fit; the plan's own layout, and what it is bound
+  // to if the call is refused, stay as they were
+  plan->no_tiles = true;
+  retile(plan);
+  const otfs_status st = solve_on_scratch(plan, y, xhat, sym, stats, stream);
+  plan->no_tiles = false;
+  retile(plan);
+  return st;
 }
 
 extern "C" otfs_status otfs_plan_set_wait_limit(otfs_plan_t* plan, int64_t wait_us) {

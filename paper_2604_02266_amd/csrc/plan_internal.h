@@ -103,6 +103,12 @@ void set_tile_cut(const TileCut& c, FrameDev* geo);
 constexpr int kApplyLdsBytes = 79 * 1024;
 TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes);
 
+// The apply cuts' launch: items, LDS bytes of a workgroup, whether it covers every frame.
+struct BoundApply {
+  int items = 0, lds = 0;
+  bool all = false;
+};
+
 // One launch of the fused kernel: the frames of one kind with their work queues.  The
 // queue ranges and cursors of launch kind k live at k * kMaxGroups.
 struct KindLaunch {
@@ -145,12 +151,13 @@ struct otfs_plan {
   int ref_xcds = 1;       // XCDs of round-robin dispatch (block order of the refresh)
   bool device_paths = false;   // the path tables were made on the device (from a pilot)
   int tile_req = 0;            // tile size asked for with otfs_plan_set_tiling (0: built-in)
-  bool no_tiles = false;       // keep the streaming kinds (workspace limit of the static scratch)
+  bool no_tiles = false;       // lay out the streaming kinds only (while the static scratch is bound)
   std::vector<otfs::TileCut> cuts;     // per frame: its register-resident cut, if any
   std::vector<otfs::TileCut> acuts;    // per frame: its apply cut, if any
   std::vector<int2> apply_items;       // {frame, tile} of the apply cuts
   int apply_lds = 0;                   // largest window of the apply cuts, bytes
   bool apply_all = false;              // every frame has an apply cut
+  otfs::BoundApply bound_apply;        // ... of the binding
   bool ref_tiles = false;              // the FP64 refresh runs on the tiles of the solve
   int nritems = 0;                     // ... one item per tile
   int2* d_ritems = nullptr;
