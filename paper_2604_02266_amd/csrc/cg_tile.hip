@@ -689,21 +689,26 @@ __device__ __forceinline__ void cg_tile_item(const FrameDev& F, int tile, int bu
 // S_p[k] of every frame with a cut: conj(R_p[k + tau]), past the row's end times
 // W[nu] (below) or conj(W[nu]) (above): with it conj(D_{p,q}) W[l']^-n' = S_p[k], where l' and
 // n' are the row and the wrap count of the gathered element, whose factor the window carries.
+// Either way that is conj(h_p) e^{-j 2 pi nu k / (MN)}, R_p continued past its row: the wrapped
+// entries are formed so in FP64 and rounded once, as those of R are (the product of the two FP32
+// tables rounded three times).
 __global__ __launch_bounds__(256) void k_tile_tables(const FrameDev* __restrict__ frames) {
   const FrameDev& F = frames[blockIdx.x];
   if (F.tk_T == 0 && F.ap_T == 0) return;
   const int M = F.M;
+  const int64_t MN = (int64_t)M * F.N;
   for (int i = (int)(blockIdx.y * blockDim.x + threadIdx.x); i < F.P * M; i += (int)(gridDim.y * blockDim.x)) {
     const int p = i / M, k = i - p * M;
     const int2 tn = F.paths[p];
     const int K = k + tn.x;
-    const bool lo = K < 0, hi = K >= M;
-    float2 c = F.rtab[p * M + (lo ? K + M : (hi ? K - M : K))];
-    c.y = -c.y;
-    if (lo || hi) {
-      float2 f = F.wtab[tn.y < 0 ? tn.y + F.N : tn.y];
-      if (hi) f.y = -f.y;
-      c = cmulf(c, f);
+    float2 c;
+    if (K >= 0 && K < M) {
+      c = F.rtab[p * M + K];
+      c.y = -c.y;
+    } else {
+      const float2 h = F.gain[p];
+      const double2 v = cmuld(make_double2((double)h.x, -(double)h.y), unit_phasor(-(int64_t)tn.y * k, MN));
+      c = make_float2((float)v.x, (float)v.y);
     }
     F.stab[i] = c;
   }

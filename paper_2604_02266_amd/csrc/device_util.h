@@ -32,6 +32,14 @@ __device__ __forceinline__ void cmacd(double2& acc, double2 c, double2 v) {
   acc.y = fma(c.x, v.y, acc.y);
   acc.y = fma(c.y, v.x, acc.y);
 }
+// e^{j 2 pi num / mn}
+__device__ __forceinline__ double2 unit_phasor(int64_t num, int64_t mn) {
+  num %= mn;
+  if (num < 0) num += mn;
+  double sn, cs;
+  sincospi(2.0 * ((double)num / (double)mn), &sn, &cs);
+  return make_double2(cs, sn);
+}
 // bf16 pair (re in the low half, im in the high half) -> complex64
 __device__ __forceinline__ float2 bf16x2_to_f2(uint32_t w) {
   return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));

@@ -2604,14 +2604,6 @@ __global__ void k_fill_u64(unsigned long long* p, int64_t n) {
 // and FP64 where the frame keeps them for the refresh), each phase from its integer
 // numerator reduced modulo MN before one FP64 sine / cosine.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ double2 unit_phasor(int64_t num, int64_t mn) {
-  num %= mn;
-  if (num < 0) num += mn;
-  double sn, cs;
-  sincospi(2.0 * ((double)num / (double)mn), &sn, &cs);
-  return make_double2(cs, sn);
-}
-
 constexpr int kPilotGroup = 8;
 __global__ __launch_bounds__(kBlock) void k_pilot_paths(FrameDev* __restrict__ frames,
                                                         const float2* __restrict__ ypilot,

@@ -117,6 +117,7 @@ struct FrameDev {
   int32_t ap_T, ap_nbr, ap_nbc, ap_tc, ap_cw;
   int32_t ref_T;          // FP64 partial sums that the refresh before a tile launch leaves
   float2* stab;           // P x M: the H^H coefficients by output column (k_tile_tables)
+  const float2* gain;     // P path gains h_p as given at otfs_plan (frames with a cut)
   // path capacity: the P given at otfs_plan; a path table estimated on the device from a
   // pilot frame (otfs_plan_paths_from_pilot) may set P to anything in [0, pcap]
   int32_t pcap;

@@ -702,6 +702,7 @@ void compute_layout(otfs_plan_t* pl) {
   L.rtab64 = refresh ? take(rt * sizeof(double2)) : 0;
   L.wtab64 = refresh ? take(wt * sizeof(double2)) : 0;
   L.paths = take(np * sizeof(int2));
+  L.gain = sb ? take(np * sizeof(float2)) : 0;
   L.aitems = pl->apply_items.empty() ? 0 : take(pl->apply_items.size() * sizeof(int2));
   L.ritems = refresh && ntiles ? take(ntiles * sizeof(int2)) : 0;
   L.uploaded = o;
@@ -1037,6 +1038,8 @@ extern "C" otfs_status otfs_plan_bind(otfs_plan_t* plan, void* ws, size_t ws_byt
                  refresh ? reinterpret_cast<double2*>(at(L.wtab64)) + wo : nullptr);
     int2* const paths = reinterpret_cast<int2*>(at(L.paths)) + po;
     for (int p = 0; p < fr.P; ++p) paths[p] = make_int2(fr.tau[p], fr.nu[p]);
+    if (L.gain) std::copy(fr.h.begin(), fr.h.end(), reinterpret_cast<float2*>(at(L.gain)) + po);
+    d.gain = reinterpret_cast<const float2*>(base + L.gain) + po;
     const size_t E = (size_t)fr.M * fr.N;
     const size_t eo = frame_vec_offset(fr.off, f);
     d.c = reinterpret_cast<float2*>(base + L.c) + eo;

@@ -25,7 +25,7 @@ struct HostFrame {
 // Byte offsets of every region of a plan workspace.
 struct Layout {
   size_t frames = 0, items = 0, qitems = 0, qrange = 0, qhead = 0, probe = 0;
-  size_t rtab = 0, wtab = 0, rtab64 = 0, wtab64 = 0, paths = 0;
+  size_t rtab = 0, wtab = 0, rtab64 = 0, wtab64 = 0, paths = 0, gain = 0;
   size_t part_pa = 0, part_cc = 0, part_d = 0, bar = 0, prog = 0, slots = 0, stab = 0, aitems = 0, ritems = 0, st = 0, abort = 0;
   size_t c = 0, p0 = 0, p1 = 0, t = 0, a = 0, u = 0, dtab = 0;
   size_t uploaded = 0;   // the regions below it are written by the host at bind
