@@ -817,9 +817,11 @@ __global__ __launch_bounds__(kBlock, 4) void k_apply_tile(const FrameDev* __rest
 hipError_t launch_apply_tile(bool adjoint, const FrameDev* frames, const int2* items, int nitems,
                              int nxcd, const float2* in, float2* out, int lds_bytes, hipStream_t s) {
   if (nitems <= 0) return hipSuccess;
-  const void* fn = adjoint ? reinterpret_cast<const void*>(&k_apply_tile<true>)
-                           : reinterpret_cast<const void*>(&k_apply_tile<false>);
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  if (lds_bytes > kApplyLdsBytes) return hipErrorInvalidValue;
+  static std::atomic<uint64_t> done[2];
+  const hipError_t e = lds_limit(adjoint ? reinterpret_cast<const void*>(&k_apply_tile<true>)
+                                         : reinterpret_cast<const void*>(&k_apply_tile<false>),
+                                 kApplyLdsBytes, done[adjoint ? 1 : 0]);
   if (e != hipSuccess) return e;
   if (adjoint)
     hipLaunchKernelGGL(k_apply_tile<true>, dim3(nitems), dim3(kBlock), lds_bytes, s, frames, items,

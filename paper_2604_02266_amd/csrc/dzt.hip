@@ -41,6 +41,8 @@ constexpr int kDztCols = 256;                    // k per workgroup (64 per wave
 constexpr int kDztFftThreads = 512;
 constexpr int kDztFftMinN = 65;                  // rule of launch_dzt
 constexpr int kDztFftMaxN = 2048;
+constexpr int kDztFftLdsBytes = 150 * 1024;
+static_assert((1 + 2 * 4) * kDztFftMaxN * (int)sizeof(float2) <= kDztFftLdsBytes, "strips of 4 columns fit");
 
 __global__ __launch_bounds__(kDztThreads) void k_dzt(int M, int N, int nframes, float sign,
                                                      const float2* __restrict__ in,
@@ -403,15 +405,15 @@ hipError_t launch_dzt(int M, int N, int nframes, bool inverse, const float2* in,
     const int bufs = P.r[2] > 1 ? 2 : 1;
     auto bytes = [&](int C) { return ((size_t)N + (size_t)bufs * N * C) * sizeof(float2); };
     P.C = 64;
-    while (P.C > 4 && bytes(P.C) > (bufs == 1 ? 80u : 150u) * 1024u) P.C /= 2;
+    while (P.C > 4 && bytes(P.C) > (bufs == 1 ? 80 * 1024u : (unsigned)kDztFftLdsBytes)) P.C /= 2;
     while (P.C > 8 && (int64_t)nframes * ((M + P.C - 1) / P.C) < 256) P.C /= 2;
     P.TY = N / P.r[0] < kDztFftThreads / P.C ? N / P.r[0] : kDztFftThreads / P.C;
     const int per_frame = (M + P.C - 1) / P.C;
     const int64_t strips = (int64_t)per_frame * nframes;
     const size_t lds = bytes(P.C);
     const int grid = (int)(strips < 1024 ? strips : 1024);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dzt_fft),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    static std::atomic<uint64_t> done;
+    const hipError_t e = lds_limit(reinterpret_cast<const void*>(&k_dzt_fft), kDztFftLdsBytes, done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_dzt_fft, dim3((unsigned)grid), dim3((unsigned)(P.C * P.TY)), lds, s, M, N,
                        strips, per_frame, P, inverse, in, out);

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "otfs.h"
 
 namespace otfs {
@@ -163,6 +165,21 @@ constexpr int kDefaultStageBytes = 0;           // LDS per workgroup for staged 
 constexpr int kResidentBytes = 40 * 1024;       // LDS of a frame solved resident in LDS
 constexpr int kStageVecs = 2;    // vectors staged at once (phase A stages c and the old p)
 
+// Allow `bytes` of dynamic LDS, the most that any launch of the kernel takes, on the current
+// device; `done` (one per kernel) has the devices where it is.  The limit belongs to the kernel
+// and not to a launch: set to each call's own size, it is another thread's between this
+// thread's call and its launch.
+inline hipError_t lds_limit(const void* fn, int bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+
 // One workgroup per item.  in/out are batch-wide complex64 buffers (frame at base + off).
 // lds_bytes: dynamic LDS for staged windows (0 if no frame is staged).  skip_cut: leave the
 // frames with an apply cut out.
@@ -202,7 +219,8 @@ constexpr int kKindDirect = 0, kKindStaged = 1, kKindResident = 2, kKindDirectFD
 constexpr int kTileElems = 16, kTileElemsSmall = 8, kTileMaxTiles = 32, kTileStride = 64;
 constexpr int kTileMeets = 4;   // meeting words per tile
 // H (H^H) of the frames with an apply cut: one workgroup per item {frame, tile}, windows of at
-// most lds_bytes.  nxcd: as for launch_refresh.
+// most lds_bytes <= kApplyLdsBytes (two workgroups per CU).  nxcd: as for launch_refresh.
+constexpr int kApplyLdsBytes = 79 * 1024;
 hipError_t launch_apply_tile(bool adjoint, const FrameDev* frames, const int2* items, int nitems,
                              int nxcd, const float2* in, float2* out, int lds_bytes, hipStream_t s);
 // Build stab of the frames with a cut from rtab and wtab.

@@ -99,8 +99,7 @@ constexpr int kTileLdsBytes = kMaxLdsBytes - 1024;   // window LDS of a tile's w
 TileCut tile_cut(const HostFrame& f, double copies, int cus);
 void set_tile_cut(const TileCut& c, FrameDev* geo);
 // The cut of the standalone applications: at most 8 elements per thread and windows of at most
-// kApplyLdsBytes (two workgroups per CU); any number of tiles.
-constexpr int kApplyLdsBytes = 79 * 1024;
+// kApplyLdsBytes; any number of tiles.
 TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes);
 
 // The apply cuts' launch: items, LDS bytes of a workgroup, whether it covers every frame.
