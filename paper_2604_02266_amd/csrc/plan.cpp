@@ -313,7 +313,7 @@ TileCut tile_cut(const HostFrame& f, double copies, int cus) {
   return best;
 }
 
-TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes) {
+TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes, double* window) {
   TileCut best;
   int tlo, thi, vlo, vhi;
   shift_ranges(f, &tlo, &thi, &vlo, &vhi);
@@ -344,10 +344,42 @@ TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes) {
         best_cost = cost;
         best = TileCut{T, nbr, nbc, tc, cw, nj * cw};
         *lds_bytes = (int)need;
+        *window = (tr + dnu) * (double)wc;
       }
     }
   }
   return best;
+}
+
+// The two estimates that choose between the apply cuts and the streaming items, in us of one
+// application of a batch of such frames.  Fitted to 1481 batches of 33 x 16 to 2048 x 256 bins, 1
+// to 32 paths, shifts of up to half a frame, in a row of 20 calls (half of them within 2 % of the
+// measured times, nine in ten within 11 and 19 %).  Tiles copy their windows, whose halos grow
+// with the shift ranges, and wait for one coefficient per path and column; the streaming items
+// gather from L2 once per element and path, two elements at a time where M allows.  Taking the
+// cuts always, 237 of those batches ran more than 8 % longer than on the streaming items (up to
+// 3.2 times: 15 frames of 1024 x 256, 2 paths far apart, 59 against 18 us) and by this rule 36 (up
+// to 1.5 times), against
+// which 19 lose more than 8 % of what the cuts gave them.  64 frames of 512 x 128, 8 paths:
+// cuts 25, streaming items 31 us.
+double apply_tile_us(const HostFrame& f, const TileCut& c, double window, double copies, int cus) {
+  const double rounds = c.T * copies / (2.0 * cus);   // two workgroups per CU
+  const double in_turn = rounds > 1 ? rounds + 0.27 * (std::ceil(rounds) - rounds) : 1.0;
+  const double kib = window * 8.0 / 1024.0;
+  const double tile = 3.1 + kib * (f.M & 1 ? 0.064 : 0.045) + 0.013 * f.P * c.elems +
+                      0.23 * f.P * std::min(1.0, rounds);
+  return std::max(10.5, 5.0 + in_turn * tile);
+}
+double apply_stream_us(const HostFrame& f, int tiles, double copies, int cus) {
+  const bool pairs = f.M % 128 == 0;
+  const int width = pairs ? f.M / 2 : f.M, rows = (f.N + tiles - 1) / tiles;
+  const int tx = strip_lanes_rule(width, rows), ty = std::max(1, kBlock / tx);
+  const double steps = (double)((width + tx - 1) / tx) * ((rows + ty - 1) / ty);
+  const double in_turn = std::max(1.0, tiles * copies / (2.0 * cus));
+  const double latency = 4.4 + (pairs ? 0.54 * f.P : 0.09 * f.P * steps * in_turn);
+  const double elems = (double)f.M * f.N * copies * 1e-6;
+  const double rate = 6.7 + ((pairs ? 0.89 : 1.06) * f.P + 1.5) * elems;
+  return std::max({10.0, latency, rate});
 }
 
 void set_tile_cut(const TileCut& c, FrameDev* geo) {
@@ -760,6 +792,8 @@ void retile(otfs_plan_t* pl) {
   } last{0, 0, 0, 0, 0, 0, 0};
   TileCut last_cut, last_acut;
   int last_lds = 0;
+  double last_window = 0;
+  double tiled_us = 0, stream_us = 0;   // estimates of an application, by elements
   const bool forms_ok = !pl->no_tiles && !(pl->opts.flags & forms) && pl->tile_req == 0 && pl->max_grid_req == 0 &&
       pl->stage_bytes == 0 && pl->win_w_req == 0;
   for (size_t f = 0; f < pl->frames.size(); ++f) {
@@ -775,7 +809,7 @@ void retile(otfs_plan_t* pl) {
       last_lds = 0;
       const double copies = (double)pl->total_elems / (double)E;
       last_cut = E <= (int64_t)kTileMaxTiles * kBlock * kTileElems ? tile_cut(fr, copies, pl->cus) : TileCut{};
-      last_acut = small ? TileCut{} : apply_cut(fr, copies, pl->cus, &last_lds);
+      last_acut = small ? TileCut{} : apply_cut(fr, copies, pl->cus, &last_lds, &last_window);
     }
     // Not for frames of less than a full tile whose rows leave lanes idle (M no multiple of
     // 64): 24 frames of 5 x 3 to 255 x 31 take 413 us against 441 us on the streaming kinds,
@@ -783,14 +817,25 @@ void retile(otfs_plan_t* pl) {
     const bool ragged = E < (int64_t)kBlock * kTileElems && fr.M % 64 != 0;
     if (!(pl->tiles[f] == 1 && pl->opts.refresh_every == 0 && small) && !ragged)
       pl->cuts[f] = last_cut;
-    if (!small) {
-      const TileCut c = last_acut;
-      pl->acuts[f] = c;
-      pl->apply_lds = std::max(pl->apply_lds, last_lds);
-      if (c.T == 0) pl->apply_all = false;
-      for (int t = 0; t < c.T; ++t) pl->apply_items.push_back(make_int2((int)f, t));
+    if (small) continue;
+    pl->acuts[f] = last_acut;
+    if (last_acut.T == 0) {
+      pl->apply_all = false;
+      continue;
     }
+    pl->apply_lds = std::max(pl->apply_lds, last_lds);
+    const double copies = (double)pl->total_elems / (double)E;
+    tiled_us += apply_tile_us(fr, last_acut, last_window, copies, pl->cus) / copies;
+    stream_us += apply_stream_us(fr, pl->tiles[f], copies, pl->cus) / copies;
   }
+  // all of the frames that have an apply cut take it, or none: a mix is two launches
+  if (tiled_us > stream_us) {
+    pl->acuts.assign(pl->frames.size(), TileCut{});
+    pl->apply_lds = 0;
+    pl->apply_all = false;
+  }
+  for (size_t f = 0; f < pl->frames.size(); ++f)
+    for (int t = 0; t < pl->acuts[f].T; ++t) pl->apply_items.push_back(make_int2((int)f, t));
   compute_layout(pl);
 }
 

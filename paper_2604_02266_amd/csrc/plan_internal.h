@@ -100,7 +100,7 @@ TileCut tile_cut(const HostFrame& f, double copies, int cus);
 void set_tile_cut(const TileCut& c, FrameDev* geo);
 // The cut of the standalone applications: at most 8 elements per thread and windows of at most
 // kApplyLdsBytes; any number of tiles.
-TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes);
+TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes, double* window);
 
 // The apply cuts' launch: items, LDS bytes of a workgroup, whether it covers every frame.
 struct BoundApply {
