@@ -313,6 +313,16 @@ TileCut tile_cut(const HostFrame& f, double copies, int cus) {
   return best;
 }
 
+// elements of a cut's window (its tallest tile)
+static double tile_window_elems(const TileCut& c, const HostFrame& f) {
+  if (c.T == 0) return 0;
+  int tlo, thi, vlo, vhi;
+  shift_ranges(f, &tlo, &thi, &vlo, &vhi);
+  int wc = (c.cw == 2 ? 128 : c.tc) + (thi - tlo) + 1;
+  wc += wc & 1;
+  return ((f.N + c.nbr - 1) / c.nbr + (vhi - vlo)) * (double)wc;
+}
+
 TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes, double* window) {
   TileCut best;
   int tlo, thi, vlo, vhi;
@@ -763,6 +773,35 @@ void compute_layout(otfs_plan_t* pl) {
   L.total = std::max<size_t>(o, 256);
 }
 
+// Whether the batch's frames keep the streaming kinds although they have cuts: all of them, since
+// a mix is two launches in turn.
+//  - Narrow frames of few paths whose one tile, 16 elements per thread, copies and multiplies row
+//    after row on one CU, while the streaming bands of the whole batch (2048 elements each) are
+//    resident at once: 20 iterations of 6 frames of 32 x 256 with 2 paths 447 us against 292, of
+//    64 x 128 340 against 284; with 6 paths, or 128 frames, the tiles win.
+//  - More tiles than CUs that mostly copy halos, of up to 16 paths: 212 frames of 201 x 116 with
+//    delays to 100 and Dopplers to +-58, windows 12.7 times their tiles, 12.4 ms against 5.0; 44
+//    of 163 x 216, 7.6 times, 2.6 against 1.6; at 6.2 times 4.4 against 5.0, and with 32 paths
+//    at 7.8 times 2.3 against 3.9.
+static bool drop_cuts(const otfs_plan_t& pl) {
+  bool narrow = true;
+  double elems = 0, paths = 0, windows = 0, tiles = 0;
+  for (size_t f = 0; f < pl.frames.size(); ++f) {
+    const TileCut& c = pl.cuts[f];
+    if (c.T == 0) continue;
+    const HostFrame& fr = pl.frames[f];
+    const double E = (double)fr.M * fr.N;
+    narrow = narrow && c.T == 1 && c.elems > kTileElemsSmall && fr.M <= 64 && fr.P <= 4;
+    elems += E;
+    paths += fr.P * E;
+    windows += c.T * tile_window_elems(c, fr);
+    tiles += c.T;
+  }
+  if (elems == 0) return false;
+  return (narrow && pl.total_elems <= (int64_t)2048 * pl.cus) ||
+         (windows > 6.5 * elems && paths <= 16 * elems && tiles > 1.5 * pl.cus);
+}
+
 // Per-frame window widths, tiles and workspace layout after a change of the tiling or the
 // windowed form.
 void retile(otfs_plan_t* pl) {
@@ -828,6 +867,7 @@ void retile(otfs_plan_t* pl) {
     tiled_us += apply_tile_us(fr, last_acut, last_window, copies, pl->cus) / copies;
     stream_us += apply_stream_us(fr, pl->tiles[f], copies, pl->cus) / copies;
   }
+  if (drop_cuts(*pl)) pl->cuts.assign(pl->frames.size(), TileCut{});
   // all of the frames that have an apply cut take it, or none: a mix is two launches
   if (tiled_us > stream_us) {
     pl->acuts.assign(pl->frames.size(), TileCut{});
