@@ -32,7 +32,9 @@ PEAK_HBM_GBS = 8000.0
 PEAK_FP32_TFLOPS = 157.3   # vector, CDNA4
 NMSE_TARGET = 1e-5
 DECISION_FP32_SLACK = 2.0 ** -20   # rounding allowance of an FP32 decision (signal units)
-KERNEL_SRC = os.path.join(ROOT, "paper_2604_02266_amd", "csrc", "kernels.hip")
+# what the solves' device code is built from: a recorded traffic figure is this code's or nobody's
+KERNEL_SRC = ("kernels.hip", "cg_tile.hip", "device_util.h", "otfs_internal.h")
+TILE_LDS_BYTES = 159 * 1024   # dynamic LDS of the register-resident tiles' launches
 MAX_WORKERS = 16          # the CPU share of one GPU on the benchmark hosts
 # FP64 refresh period per workload (the 128 x (1024, 256) configuration asks for 10)
 REFRESH = {"batch128_1024x256": 10}
@@ -54,8 +56,11 @@ BYTES_INIT, BYTES_ITER, BYTES_FINISH, BYTES_REFRESH = 32.0, 96.0, 25.0, 40.0
 
 
 def kernel_source_sha() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in KERNEL_SRC:
+        with open(os.path.join(ROOT, "paper_2604_02266_amd", "csrc", name), "rb") as f:
+            h.update(name.encode() + b"\0" + f.read())
+    return h.hexdigest()[:16]
 
 
 # ----------------------------------------------------------------------------------------
@@ -246,8 +251,12 @@ def solve_block(otfs, O, np, torch, name, frames, ys, refs, steps, warmup, refre
     parity = check_against_oracle(O, np, frames, offs, xh, dh, refs)
     lb = launch_bytes(specs, iters, refresh)
     f32, f64 = launch_flops(specs, iters, refresh)
-    tiles = plan.tuned is None   # the built-in kind of these frames; a tuned shape streams
+    # register-resident tiles, or a streaming kind (a tuned shape, frames beyond 32 tiles)
+    info = plan.info()
+    tiles = plan.tuned is None and info.launches == 1 and info.lds_bytes == TILE_LDS_BYTES
     kname = "k_cg_tile" if tiles else "k_cg_fused"
+    if refresh:
+        kname += " + k_refresh_tile" if tiles else " + k_refresh_u + k_refresh_c"
     kms, solve_ms = kernel_times(otfs, specs, y, xhat, dec, stats, steps, refresh, torch)
     kavg = float(np.mean(kms))
     achieved = (f32 + f64) / (kavg * 1e-3) / 1e12
@@ -268,9 +277,8 @@ def solve_block(otfs, O, np, torch, name, frames, ys, refs, steps, warmup, refre
         # units bound them (the refresh's FP64 operations count at the same rate)
         "roofline": {"bound": "fp32 vector", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
-                     "traffic": load_traffic(name, refresh),
-                     "kernel": kname + ((" + k_refresh_tile" if tiles else " + k_refresh_u + k_refresh_c")
-                                        if refresh else ""),
+                     "traffic": load_traffic(name, refresh, kname),
+                     "kernel": kname,
                      "kernel_ms": kavg, "fp32_ops_per_launch": f32, "fp64_ops_per_launch": f64,
                      "streaming_bytes_per_launch": lb,
                      "streaming_GBs": lb / (kavg * 1e-3) / 1e9, "copy_GBs": copy_gbs},
@@ -340,13 +348,16 @@ def plan_elems(specs):
     return float(sum(sp.E for sp in specs))
 
 
-def load_traffic(workload, refresh):
+def load_traffic(workload, refresh, kernel):
+    """Bytes of one solve as the counters recorded them, if they were recorded for this kernel,
+    built from the present sources, with this refresh period."""
     path = os.path.join(ROOT, "profiles", f"traffic_{workload}.json")
     if not os.path.exists(path):
         return None
     with open(path) as f:
         t = json.load(f)
-    if t.get("kernel_source_sha") != kernel_source_sha() or int(t.get("refresh_every", 0)) != refresh:
+    if (t.get("kernel_source_sha") != kernel_source_sha() or t.get("kernel") != kernel
+            or int(t.get("refresh_every", 0)) != refresh):
         return None
     return t.get("traffic_bytes_per_launch")
 
