@@ -303,7 +303,7 @@ __device__ __forceinline__ T shared_ld(const T* p) {
 // after which nothing was invalidated; else a launch boundary or an acquire fence orders them,
 // and the L1 serves the 512 threads' reads of one word.  Read past it all the same, the unfused
 // form on 256 tiles per frame took 15.4 ms instead of 8.3 (16 frames of 1024 x 256, 10
-// iterations), and the fused form with device-wide fences 94.8 ms instead of 69.3 (20
+// iterations), and the fused form with device-wide fences 95.4 ms instead of 68.8 (20
 // iterations).  By whole waves, one word per lane and 256 readlanes: 9.9 and 75.8 ms.
 template <bool PAST_L1, class V>
 __device__ __forceinline__ V part_ld(const V* p) {

@@ -1595,7 +1595,7 @@ __device__ __forceinline__ bool frame_windows_fit(const FrameDev& F) {
 
 // GM: where the gathers read from (kGmDirect, kGmStaged, kGmLds).  FDIR: the H pass forms
 // p' = c + beta p inside its gathers (direct-fd kind).
-template <int SD, int GM, bool FDIR = false>
+template <int SD, int GM, bool FDIR = false, bool AGENT = false>
 __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, int budget, const Bases& B,
                         const LaunchCtx& L, float* red, int* sflag, float2* lds) {
   // the stored-table reads leave fewer registers for gathers in flight
@@ -1622,12 +1622,7 @@ __device__ __forceinline__ void cg_item(const FrameDev& F, const WorkItem& wi, i
     nbar += (unsigned)T;
     return frame_barrier(F.bar, nbar, L.xcd_local != 0, L.abort_flag, L.timeout, sflag);
   };
-  // after bar(), whose device-wide form invalidates the L1 (the stored tables' kinds, whose
-  // registers are full, keep one form: 0.7 % slower with both)
-  auto sum_tiles = [&](const float* part) {
-    if (SD == kDNone && !L.xcd_local) return tile_sum<false>(part, T);
-    return tile_sum<true>(part, T);
-  };
+  auto sum_tiles = [&](const float* part) { return tile_sum<!AGENT>(part, T); };
   // tiles whose rows the H pass (rows l - nu) and the H^H pass (rows l + nu) read
   const int span = le - lb + (F.nu_hi - F.nu_lo);
   const TileRange rd_h = tiles_of_rows(lb - F.nu_hi, span, F.N, T);
@@ -1947,9 +1942,6 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     nbar += (unsigned)T;
     return frame_barrier(F.bar, nbar, L.xcd_local != 0, L.abort_flag, L.timeout, sflag);
   };
-  auto sum_tiles = [&](const float* part) {   // after bar(), whose device-wide form invalidates the L1
-    return L.xcd_local ? tile_sum<true>(part, T) : tile_sum<false>(part, T);
-  };
   // strips whose columns the H^H pass gathers: [k0 + tau_lo, k0 + W - 1 + tau_hi] (mod M)
   const TileRange rd_hh = tiles_of_rows(k0 + F.tau_lo, W + (F.tau_hi - F.tau_lo), M, T);
   unsigned npub = 0;
@@ -1992,7 +1984,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     const float bs = block_sum(acc, red);
     if (threadIdx.x == 0) F.part_cc[wi.tile] = bs;
     if (!bar()) return fail_timeout();
-    const float cn0 = sum_tiles(F.part_cc);
+    const float cn0 = tile_sum<true>(F.part_cc, T);
     s.init = 1;
     s.iter = 0;
     s.pbuf = 0;
@@ -2050,7 +2042,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
     if (!bar()) return fail_timeout();
     s.pbuf ^= 1;
     s.pending = 0;
-    const float den = sum_tiles(F.part_pa);
+    const float den = tile_sum<true>(F.part_pa, T);
     const float alpha = s.cn / den;
     if (!(den > 0.f) || !isfinite(alpha)) {
       const int st = (isfinite(den) && isfinite(s.cn)) ? OTFS_FRAME_BREAKDOWN
@@ -2085,7 +2077,7 @@ __device__ void cg_item_win(const FrameDev& F, const WorkItem& wi, int budget, c
       if (threadIdx.x == 0) F.part_cc[wi.tile] = bs;
     }
     if (!bar()) return fail_timeout();
-    const float cn_new = sum_tiles(F.part_cc);
+    const float cn_new = tile_sum<true>(F.part_cc, T);
     s.iter = xi;
     s.alpha = alpha;
     s.rel = sqrtf(cn_new / s.cn0);
@@ -2267,7 +2259,11 @@ constexpr int fused_min_waves(int kind, int sd) {
                                       ? OTFS_FUSED_MIN_WAVES
                                       : OTFS_LDS_MIN_WAVES);
 }
-template <int SD, int KIND>
+// AGENT: the launch waits at device-wide fences (L.xcd_local = 0), which invalidate the L1, so the
+// partial sums are read through it (direct kinds, whose frames may then have more tiles than one
+// XCD holds).  A kernel of its own: with both reads in one, 16 pilot-estimated frames of 512 x
+// 128 took 643 us instead of 640 and stored tables 0.7 % longer.
+template <int SD, int KIND, bool AGENT = false>
 __global__ __launch_bounds__(kBlock, fused_min_waves(KIND, SD)) void k_cg_fused(const FrameDev* __restrict__ frames,
                                                      const WorkItem* __restrict__ items,
                                                      const int32_t* __restrict__ qitems,
@@ -2305,8 +2301,7 @@ __global__ __launch_bounds__(kBlock, fused_min_waves(KIND, SD)) void k_cg_fused(
       cg_item_win(F, wi, budget, B, L, red, &sflag, stage_lds);
     else
       cg_item<SD, KIND == kKindStaged ? kGmStaged : (KIND == kKindLds ? kGmLds : kGmDirect),
-              KIND == kKindDirectFD>(F, wi, budget, B, L, red, &sflag,
-                                                              stage_lds);
+              KIND == kKindDirectFD, AGENT>(F, wi, budget, B, L, red, &sflag, stage_lds);
     __syncthreads();
   }
 }
@@ -2957,11 +2952,11 @@ static uint64_t wait_ticks(int64_t wait_us) {
   return (uint64_t)wait_us * wallclock_ticks_per_us();
 }
 
-template <int SD, int KIND>
+template <int SD, int KIND, bool AGENT = false>
 static void launch_fused_t(const FrameDev* frames, const WorkItem* items, const int32_t* qitems,
                            const int2* qrange, unsigned* qhead, int ngroups, int grid, int budget,
                            const Bases& bases, const LaunchCtx& L, int lds_bytes, hipStream_t s) {
-  hipLaunchKernelGGL((k_cg_fused<SD, KIND>), dim3(grid), dim3(kBlock), lds_bytes, s, frames, items,
+  hipLaunchKernelGGL((k_cg_fused<SD, KIND, AGENT>), dim3(grid), dim3(kBlock), lds_bytes, s, frames, items,
                      qitems, qrange, qhead, ngroups, budget, bases, L);
 }
 
@@ -2981,6 +2976,13 @@ static const void* fused_fn(int kind, int sd) {
   if (sd == kDBf16) return reinterpret_cast<const void*>(&k_cg_fused<kDBf16, kKindDirect>);
   if (sd == kDC64) return reinterpret_cast<const void*>(&k_cg_fused<kDC64, kKindDirect>);
   return reinterpret_cast<const void*>(&k_cg_fused<kDNone, kKindDirect>);
+}
+
+static const void* fused_agent_fn(int kind, int sd) {
+  if (sd != kDNone) return nullptr;
+  if (kind == kKindDirectFD) return reinterpret_cast<const void*>(&k_cg_fused<kDNone, kKindDirectFD, true>);
+  if (kind == kKindDirect) return reinterpret_cast<const void*>(&k_cg_fused<kDNone, kKindDirect, true>);
+  return nullptr;
 }
 
 hipError_t launch_cg_fused(int kind, int sd, const FrameDev* frames, const WorkItem* items,
@@ -3005,7 +3007,10 @@ hipError_t launch_cg_fused(int kind, int sd, const FrameDev* frames, const WorkI
       launch_fused_t<kDNone, kKindWindowed>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, lds_bytes, s);
       break;
     case kKindDirectFD:
-      launch_fused_t<kDNone, kKindDirectFD>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
+      if (xcd_local)
+        launch_fused_t<kDNone, kKindDirectFD>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
+      else
+        launch_fused_t<kDNone, kKindDirectFD, true>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
       break;
     case kKindStaged:
       launch_fused_t<kDNone, kKindStaged>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, lds_bytes, s);
@@ -3023,8 +3028,10 @@ hipError_t launch_cg_fused(int kind, int sd, const FrameDev* frames, const WorkI
         launch_fused_t<kDBf16, kKindDirect>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
       else if (sd == kDC64)
         launch_fused_t<kDC64, kKindDirect>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
-      else
+      else if (xcd_local)
         launch_fused_t<kDNone, kKindDirect>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
+      else
+        launch_fused_t<kDNone, kKindDirect, true>(frames, items, qitems, qrange, qhead, ngroups, grid, budget, bases, L, 0, s);
   }
   return hipGetLastError();
 }
@@ -3065,6 +3072,12 @@ int fused_blocks_per_cu(int kind, int sd, int lds_bytes) {
     (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kBlock, lds_bytes) != hipSuccess)
     n = 0;
+  // which of the direct kinds' two kernels runs is decided after this: the grid fits both
+  if (const void* agent = fused_agent_fn(kind, sd)) {
+    int na = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&na, agent, kBlock, lds_bytes) != hipSuccess) na = 0;
+    n = na < n ? na : n;
+  }
   if (keep) {
     std::lock_guard<std::mutex> guard(mu);
     kept[dev][kind][sd] = n;
