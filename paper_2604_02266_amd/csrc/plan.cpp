@@ -362,34 +362,32 @@ TileCut apply_cut(const HostFrame& f, double copies, int cus, int* lds_bytes, do
 }
 
 // The two estimates that choose between the apply cuts and the streaming items, in us of one
-// application of a batch of such frames.  Fitted to 1481 batches of 33 x 16 to 2048 x 256 bins, 1
-// to 32 paths, shifts of up to half a frame, in a row of 20 calls (half of them within 2 % of the
-// measured times, nine in ten within 11 and 19 %).  Tiles copy their windows, whose halos grow
-// with the shift ranges, and wait for one coefficient per path and column; the streaming items
-// gather from L2 once per element and path, two elements at a time where M allows.  Taking the
-// cuts always, 237 of those batches ran more than 8 % longer than on the streaming items (up to
-// 3.2 times: 15 frames of 1024 x 256, 2 paths far apart, 59 against 18 us) and by this rule 36 (up
-// to 1.5 times), against
-// which 19 lose more than 8 % of what the cuts gave them.  64 frames of 512 x 128, 8 paths:
-// cuts 25, streaming items 31 us.
+// application of a batch of such frames.  Fitted to the GPU times (20 captured calls in a row) of
+// 1772 batches of 33 x 16 to 2048 x 256 bins, 1 to 32 paths, shifts of up to half a frame; half of
+// them are within 10 % of the measured times, nine in ten within 22 and 27 %.  Tiles copy their
+// windows, whose halos grow with the shift ranges, and wait for one coefficient per path and
+// column; the streaming items gather from L2 once per element and path, two elements at a time
+// where M allows.  With the cuts always, 293 of the 676 batches with delays to M / 8, Dopplers to
+// +-N / 4 and up to 16 paths ran more than 8 % longer than on the streaming items (up to 2.4
+// times; of all the batches up to 3.2: 15 frames of 1024 x 256, 2 paths far apart, 59 against 18
+// us), and by this rule 19 (up to 1.6 times), against which 38 lose more than 8 % of what the
+// cuts gave them.  64 frames of 512 x 128, 8 paths: cuts 25, streaming items 31 us.
 double apply_tile_us(const HostFrame& f, const TileCut& c, double window, double copies, int cus) {
   const double rounds = c.T * copies / (2.0 * cus);   // two workgroups per CU
-  const double in_turn = rounds > 1 ? rounds + 0.27 * (std::ceil(rounds) - rounds) : 1.0;
+  const double in_turn = rounds > 1 ? rounds + 0.45 * (std::ceil(rounds) - rounds) : 1.0;
   const double kib = window * 8.0 / 1024.0;
-  const double tile = 3.1 + kib * (f.M & 1 ? 0.064 : 0.045) + 0.013 * f.P * c.elems +
-                      0.23 * f.P * std::min(1.0, rounds);
-  return std::max(10.5, 5.0 + in_turn * tile);
+  return 3.3 + in_turn * (1.6 + kib * (f.M & 1 ? 0.092 : 0.072) + f.P * (0.1 + 0.27 * std::min(1.0, rounds)));
 }
 double apply_stream_us(const HostFrame& f, int tiles, double copies, int cus) {
   const bool pairs = f.M % 128 == 0;
   const int width = pairs ? f.M / 2 : f.M, rows = (f.N + tiles - 1) / tiles;
   const int tx = strip_lanes_rule(width, rows), ty = std::max(1, kBlock / tx);
-  const double steps = (double)((width + tx - 1) / tx) * ((rows + ty - 1) / ty);
+  // elements of one thread
+  const double each = (double)((width + tx - 1) / tx) * ((rows + ty - 1) / ty) * (pairs ? 2 : 1);
   const double in_turn = std::max(1.0, tiles * copies / (2.0 * cus));
-  const double latency = 4.4 + (pairs ? 0.54 * f.P : 0.09 * f.P * steps * in_turn);
-  const double elems = (double)f.M * f.N * copies * 1e-6;
-  const double rate = 6.7 + ((pairs ? 0.89 : 1.06) * f.P + 1.5) * elems;
-  return std::max({10.0, latency, rate});
+  const double latency = 3.1 + in_turn * f.P * (0.105 * each + (pairs ? 0.13 : 0.0));
+  const double rate = 3.8 + ((pairs ? 1.04 : 1.25) * f.P + 1.7) * ((double)f.M * f.N * copies * 1e-6);
+  return std::max(latency, rate);
 }
 
 void set_tile_cut(const TileCut& c, FrameDev* geo) {
