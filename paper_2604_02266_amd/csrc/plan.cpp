@@ -690,8 +690,11 @@ otfs_status probe_xcds(int device, void* scratch_dev, hipStream_t s, XcdInfo* ou
   XcdInfo info;
   info.nxcd = ok ? mx + 1 : 1;
   info.round_robin = ok && info.nxcd > 1;
+  // from any first XCD: each hardware queue goes on where it stopped, so the first launch of a
+  // process starts at XCD 0, one after a graph's replay or beside another stream elsewhere (the
+  // kernels read their own XCC id, and items are grouped by block index modulo nxcd)
   for (int b = 0; b < kProbeBlocks && info.round_robin; ++b)
-    if (ids[b] != b % info.nxcd) info.round_robin = false;
+    if (ids[b] != (ids[0] + b) % info.nxcd) info.round_robin = false;
   if (device >= 0 && device < 64) {
     cached_n[device] = info.nxcd;
     cached_rr[device] = info.round_robin ? 1 : 0;

@@ -73,7 +73,7 @@ bool make_queues(const std::vector<double>& work, const std::vector<int>& tile_b
 // XCD layout of a device, found once per device by a probe launch.
 struct XcdInfo {
   int nxcd = 1;          // number of XCDs seen
-  bool round_robin = false;  // workgroup b ran on XCD b % nxcd for every probed b
+  bool round_robin = false;  // workgroup b ran on XCD (first + b) % nxcd for every probed b
 };
 otfs_status probe_xcds(int device, void* scratch_dev, hipStream_t s, XcdInfo* out);
 void retile(struct ::otfs_plan* pl);
