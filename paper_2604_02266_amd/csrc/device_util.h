@@ -32,13 +32,16 @@ __device__ __forceinline__ void cmacd(double2& acc, double2 c, double2 v) {
   acc.y = fma(c.x, v.y, acc.y);
   acc.y = fma(c.y, v.x, acc.y);
 }
-// e^{j 2 pi num / mn}
-__device__ __forceinline__ double2 unit_phasor(int64_t num, int64_t mn) {
-  num %= mn;
-  if (num < 0) num += mn;
+// e^{j 2 pi num / mn}, num in [0, mn)
+__device__ __forceinline__ double2 reduced_phasor(int64_t num, int64_t mn) {
   double sn, cs;
   sincospi(2.0 * ((double)num / (double)mn), &sn, &cs);
   return make_double2(cs, sn);
+}
+// the same for any num
+__device__ __forceinline__ double2 unit_phasor(int64_t num, int64_t mn) {
+  num %= mn;
+  return reduced_phasor(num < 0 ? num + mn : num, mn);
 }
 // bf16 pair (re in the low half, im in the high half) -> complex64
 __device__ __forceinline__ float2 bf16x2_to_f2(uint32_t w) {
