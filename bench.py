@@ -318,8 +318,6 @@ def plain_block(otfs, O, np, torch, frames, ys, refs, refresh, offs, reps=3):
             "note": "no FP64 refresh in the plain form" if refresh else ""}
 
 
-
-
 def dzt_block(otfs, np, torch, M, N, nframes, reps=10):
     """The front end's DZT (Eq. zak) of a batch of time-domain frames, by passes of short DFTs:
     16 M N bytes per frame, timed with HIP events."""

@@ -190,7 +190,10 @@ otfs_status otfs_plan_info(const otfs_plan_t* plan, otfs_plan_info_t* info);
 
 /* Change the tiling (target elements per workgroup tile, >= 1, or 0 for the built-in
  * rule) and the workgroup cap of the fused kernel (0 = occupancy limit).  The built-in rule
- * keeps the CG vectors of most frames in the registers of up to 32 workgroups; a tiling, a
+ * keeps the CG vectors of most frames in the registers of up to 32 workgroups, one per CU of
+ * one XCD; batches whose sizes make that the slower form (small batches of narrow frames of
+ * few paths, large ones whose paths reach across most of the frame) and frames of less than
+ * 8192 elements with M no multiple of 64 stay on the streaming kinds.  A tiling, a
  * workgroup cap, staging, a window, or one of the flags that name a form (OTFS_LDS_GATHER,
  * OTFS_SPLIT_DIRECTION, OTFS_NO_LDS_RESIDENT, OTFS_AGENT_BARRIER, a stored D) selects the
  * streaming kinds, and so does a path table made on the device from a pilot.  Takes effect at
@@ -217,7 +220,9 @@ otfs_status otfs_plan_set_staging(otfs_plan_t* plan, int32_t lds_bytes);
 
 /* ------------------------------------------------------------------------------------ */
 /* Operator applications (Eq. sparse_mvm and Eq. sparse_herm_mvm), every frame of the   */
-/* bound batch in one launch.  x_dev / y_dev: total_elems complex64 each, distinct.       */
+/* bound batch in one launch.  x_dev / y_dev: total_elems complex64 each, distinct.  The  */
+/* built-in launch shape takes the faster of two forms by the batch's sizes; their sums   */
+/* differ in rounding only.                                                               */
 /* ------------------------------------------------------------------------------------ */
 otfs_status otfs_apply_H(const otfs_plan_t* plan, const void* x_dev, void* y_dev, void* stream);
 otfs_status otfs_apply_HH(const otfs_plan_t* plan, const void* y_dev, void* x_dev, void* stream);
@@ -232,9 +237,12 @@ otfs_status otfs_apply_HH(const otfs_plan_t* plan, const void* y_dev, void* x_de
  * c = H^H (y - H x) - lam x; frames of the windowed-pairs kind (OTFS_LDS_GATHER) whose LDS
  * windows fit form it inside the fused launch instead, and when every frame is of that kind
  * and the path tables are the host's, a solve is one launch.  The fused launches expect the
- * GPU to themselves: a frame's
- * tiles must all be resident at once, and work from other streams that keeps some of them
- * waiting makes the frame report OTFS_FRAME_TIMEOUT after the wait bound.  y_dev: total_elems complex64 (bf16 pairs with OTFS_Y_BF16);
+ * GPU to themselves: a frame's tiles must all be resident at once, and work from other
+ * streams that keeps some of them waiting makes the frame report OTFS_FRAME_TIMEOUT after the
+ * wait bound.  Frames solved in registers may ask for every CU of an XCD, so solves on several
+ * streams are to be ordered one after the other; a tiling of the caller's own
+ * (otfs_plan_set_tiling) asks for as many workgroups per frame as it has tiles.
+ * y_dev: total_elems complex64 (bf16 pairs with OTFS_Y_BF16);
  * xhat_dev: total_elems complex64 output; sym_dev: total_elems uint8 hard decisions
  * i_I * sqrt(Q) + i_Q (Eq. demod; nullable; frames with qam = 0 are left untouched);
  * stats_dev: nframes otfs_frame_stats (nullable). */

@@ -10,8 +10,8 @@ on the frame shapes, the path count, the batch size and the modes (refresh, stor
 tune() searches these knobs for one batch on the current device: every candidate plan
 solves the same received frames; its fused solve is timed with HIP events on the launch
 stream (median of `reps` after a warm-up) and its estimate is checked against the default
-plan's (the first candidate: the library's built-in launch shape) (NMSE <= 1e-6: a candidate changes the rounding order of the per-tile partial
-sums, nothing else).  The winner and the whole search table are stored in tuned.json
+plan's.  That plan, the first candidate, has the library's built-in launch shape.  The bound
+is NMSE <= 1e-6: a candidate changes the order of the sums, nothing else.  The winner and the whole search table are stored in tuned.json
 beside this module, keyed by the batch signature (frame shapes, batch-size bucket, path
 bucket, modes).  Plan applies a stored winner by default (lookup()), and the serving
 loop takes per-shape tiles from the same file (serving_tiles()).

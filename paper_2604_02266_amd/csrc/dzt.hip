@@ -394,9 +394,9 @@ hipError_t launch_dzt(int M, int N, int nframes, bool inverse, const float2* in,
   if (nb > 0x7fffffff) return hipErrorInvalidValue;
   if (N > kDztMaxN) return hipErrorInvalidValue;
   // From 65 bins on the passes are the faster (80 bins: 67 -> 25 us for 100 frames of 1024
-  // columns).  Below, k_dzt stays although it is up to 2.5 times slower at full batches (64 bins:
-  // 105 against 43 us, 16 bins: equal): its rounding is what the receiver's short frames are
-  // decided on, and their decisions stay as they were.  Above 2048 bins a strip of 4 columns
+  // columns).  Below, speed does not draw the line: at full batches k_dzt is up to 2.5 times
+  // slower (64 bins: 105 against 43 us, 16 bins: equal).  It stays because the receiver's short
+  // frames are decided on its rounding; the passes would move single decisions there.  Above 2048 bins a strip of 4 columns
   // no longer fits the LDS twice, and a prime factor above 13 has no short DFT.
   DztPlan P;
   if (N >= kDztFftMinN && N <= kDztFftMaxN && dzt_radices(N, P.r)) {

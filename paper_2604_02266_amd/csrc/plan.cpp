@@ -814,8 +814,9 @@ void retile(otfs_plan_t* pl) {
   make_tiles(pl->frames, pl->tile_elems, pl->items, pl->tile_base, pl->tiles, &pl->winw);
   // Register-resident tiles: the built-in choice whenever the caller asked for no launch
   // shape or form of its own, for every frame that a cut of at most kTileMaxTiles tiles holds
-  // and that is not small enough for one workgroup's LDS (64 frames of 512 x 128: 1.73 ms
-  // against 3.89 ms on the streaming kinds; one such frame: 0.60 against 1.38 ms).
+  // and that is not small enough for one workgroup's LDS (64 frames of 512 x 128: 1.64 ms
+  // against 3.89 ms on the streaming kinds; one such frame: 0.57 against 1.38 ms), less the
+  // batches that drop_cuts() takes back.
   pl->cuts.assign(pl->frames.size(), TileCut{});
   pl->acuts.assign(pl->frames.size(), TileCut{});
   pl->apply_items.clear();
@@ -852,8 +853,10 @@ void retile(otfs_plan_t* pl) {
       last_acut = small ? TileCut{} : apply_cut(fr, copies, pl->cus, &last_lds, &last_window);
     }
     // Not for frames of less than a full tile whose rows leave lanes idle (M no multiple of
-    // 64): 24 frames of 5 x 3 to 255 x 31 take 413 us against 441 us on the streaming kinds,
-    // whose sums these small, often ill-conditioned frames keep bit for bit.
+    // 64): on tiles 24 frames of 5 x 3 to 255 x 31 gain little (419 against 450 us), and these
+    // frames, often ill-conditioned, keep the estimates and decisions they had.  The error
+    // against a 64-bit solve does not decide it: equal on the mean over 40 batches, 0.59 to
+    // 1.28 times in single ones, one decision in all of them another.
     const bool ragged = E < (int64_t)kBlock * kTileElems && fr.M % 64 != 0;
     if (!(pl->tiles[f] == 1 && pl->opts.refresh_every == 0 && small) && !ragged)
       pl->cuts[f] = last_cut;
